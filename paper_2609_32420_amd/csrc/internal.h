@@ -80,6 +80,21 @@ __device__ inline uint64_t wave_max_u64(uint64_t x) {
   return wave_reduce_bits(x, [](uint64_t a, uint64_t b) { return b > a ? b : a; });
 }
 
+// Inclusive scan over the 64 lanes of a wave: four DPP row shifts (by 1, 2,
+// 4, 8 lanes; lanes shifted in from outside the 16-lane row read 0) scan each
+// row, then two row broadcasts add lane 15 into row 1, lane 47 into row 3
+// and lane 31 into rows 2 and 3.
+__device__ inline int wave_incl_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);  // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);  // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);  // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast:15
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast:31
+  return x;
+}
+__device__ inline int wave_sum_i32(int x) { return __builtin_amdgcn_readlane(wave_incl_scan(x), 63); }
+
 // ---- block mask builder ----------------------------------------------------
 // Pools Q_hist and K_hist per block (fp64 means over valid tokens).
 //   qbar:  fp64 [BH][nB][d]   (row-major)

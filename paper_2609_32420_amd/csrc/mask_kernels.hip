@@ -7,6 +7,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 namespace carnator {
 namespace {
 
@@ -88,8 +90,11 @@ __global__ void __launch_bounds__(256) pool_kernel(View q, View k, int H, int N,
 // reads back the exact logit of its block.
 __device__ inline uint64_t sel_key(double s, int j) {
   const uint64_t b = (uint64_t)__double_as_longlong(s);
-  const uint64_t m = (b >> 63) ? ~b : (b | 0x8000000000000000ull);
-  return (m & ~0x7ffull) | (uint64_t)(2047 - j);
+  const uint32_t hi = (uint32_t)(b >> 32);
+  const uint32_t neg = (uint32_t)((int32_t)hi >> 31);  // all ones for a negative logit
+  const uint32_t kh = hi ^ (neg | 0x80000000u);
+  const uint32_t kl = (((uint32_t)b ^ neg) & ~0x7ffu) | (uint32_t)(2047 - j);
+  return ((uint64_t)kh << 32) | kl;
 }
 __device__ inline int sel_index(uint64_t k) { return 2047 - (int)(k & 0x7ff); }
 // The logit a selection key stands for, up to its low 11 bits (used only to pick
@@ -97,6 +102,46 @@ __device__ inline int sel_index(uint64_t k) { return 2047 - (int)(k & 0x7ff); }
 __device__ inline double key_value(uint64_t k) {
   const uint64_t b = (k >> 63) ? (k & 0x7fffffffffffffffull) : ~k;
   return __longlong_as_double((long long)b);
+}
+
+// exp(x) for x <= 0 (NaN gives NaN, anything below the subnormals 0): x = n ln 2 + r
+// with n the nearest integer (ln 2 in two parts), the Taylor series of exp(r)
+// to r^13 (|r| <= 0.347: truncation 4e-18, 0.02 ulp) and a scaling by 2^n.
+// Free of branches and with its coefficients in scalar registers, so the
+// exponentials of a lane's positions interleave: through the library's exp
+// each position was a predicated block of its own that first moved every
+// coefficient into vector registers (42 vector instructions against 22).
+struct ExpCoef {
+  double c[12];  // 1 / 13!, ..., 1 / 2!
+  double log2e, ln2hi, ln2lo;
+};
+__device__ inline double in_sgpr(double x) {
+  asm("" : "+s"(x));
+  return x;
+}
+__device__ inline ExpCoef exp_coef() {
+  ExpCoef e;
+  constexpr double f[12] = {1.0 / 6227020800.0, 1.0 / 479001600.0, 1.0 / 39916800.0, 1.0 / 3628800.0,
+                            1.0 / 362880.0,     1.0 / 40320.0,     1.0 / 5040.0,     1.0 / 720.0,
+                            1.0 / 120.0,        1.0 / 24.0,        1.0 / 6.0,        1.0 / 2.0};
+#pragma unroll
+  for (int i = 0; i < 12; ++i) e.c[i] = in_sgpr(f[i]);
+  e.log2e = in_sgpr(1.4426950408889634074);
+  e.ln2hi = in_sgpr(0x1.62e42fefa0000p-1);        // ln 2 to 36 bits: n ln2hi is exact
+  e.ln2lo = in_sgpr(0x1.cf79abc9e3b3ap-40);       // ln 2 - ln2hi
+  return e;
+}
+__device__ inline double exp_neg(double x, const ExpCoef &e) {
+  x = x < -800.0 ? -800.0 : x;
+  const double n = __builtin_rint(x * e.log2e);
+  double r = __builtin_fma(-n, e.ln2hi, x);
+  r = __builtin_fma(-n, e.ln2lo, r);
+  double p = e.c[0];
+#pragma unroll
+  for (int i = 1; i < 12; ++i) p = __builtin_fma(p, r, e.c[i]);
+  p = __builtin_fma(p, r, 1.0);
+  p = __builtin_fma(p, r, 1.0);
+  return __builtin_ldexp(p, (int)n);
 }
 
 // Bisection state of one row (the same in every lane): mass(key >= lo) >=
@@ -188,8 +233,16 @@ __device__ inline uint64_t bisect_result(const uint64_t (&key)[EE], int c_off, c
   return kstar;
 }
 
-// One workgroup of W waves per (bh, R consecutive query blocks), W = R or
-// R / 2 (then each wave selects two rows).
+// The positions per lane that select_kernel is instantiated for; the one
+// before E (rows taken by E have more than 64 sel_prev(E) blocks).
+constexpr int kSelE[] = {0, 1, 2, 3, 4, 6, 8, 10, 12, 16, 24, 32};
+constexpr int sel_prev(int e) {
+  int p = 0;
+  for (int x : kSelE) p = x < e ? x : p;
+  return p;
+}
+
+// One workgroup of W = R waves per (bh, R consecutive query blocks).
 //
 // Phase 1, s_ij = sigma <qbar_i, kbar_j>: the R pooled query rows sit in LDS;
 // a wave takes 16 key blocks at a time and forms the 16 x 16 tile of dot
@@ -201,6 +254,15 @@ __device__ inline uint64_t bisect_result(const uint64_t (&key)[EE], int c_off, c
 // its channels in the same order.  With R = 8 the upper half of the tile
 // repeats row R - 1 and is not stored.  Phase 2: wave w selects rows w,
 // w + W, ... of the workgroup (E = positions per lane, 64 E >= nB).
+//
+// Bound: at nB = 591 (40 heads) 192 us, was 244 us: the score tiles with
+// their kbar loads (0.9 GB through the L2) 119 us, 74 us of it the fp64
+// matrix cores (2048 cycles a tile), and the selection 73 us of dependent
+// vector work, ~1330 vector instructions a row; one workgroup per CU (its
+// LDS), so the two do not overlap.  The gain is one row per wave on 16 waves
+// (244 -> 215 us) and a selection free of branches per position: rows padded to 64 E
+// so that every logit is loaded at once, exp_neg, and the tie ranks taken on
+// whole 64-bit words.  At nB <= 256 one workgroup's latency (20 us).
 // MASS: the rows are given, as block masses [BH][nB][nB] at qbar (kbar and
 // sigma unused): phase 1 copies the workgroup's rows into LDS and phase 2
 // selects on the masses themselves instead of the softmax of logits.
@@ -210,15 +272,16 @@ __global__ void __launch_bounds__(64 * W) select_kernel(const double *__restrict
                                                         double sigma, double tau,
                                                         uint8_t *__restrict__ mask,
                                                         uint64_t *__restrict__ bits, int BH) {
-  // LDS: [R][nB] logits, then the R pooled query rows, QS doubles apart (a
+  // LDS: [R][NP] logits (NP = 64 E, -inf past nB), then the R pooled query rows, QS doubles apart (a
   // 16-byte pad spreads the 16 rows read by one MFMA step over the banks),
   // at least W * 128 doubles
-  constexpr int QS = D + 2;
+  constexpr int QS = D + 2, NP = 64 * E;
   extern __shared__ double sc[];
   // Workgroups are dealt to the 8 XCDs in turn.  Logical workgroup
   // (L mod 8) ceil(G / 8) + L / 8 gives each XCD a contiguous run of
   // (head, row block) pairs, so an XCD's L2 fetches the kbar of about
   // BH / 8 heads instead of all of them.
+  static_assert(W == R, "one row per wave in phase 2");
   const int nbx = (nB + R - 1) / R;
   const int G = nbx * BH;
   const int per = (G + 7) / 8;
@@ -233,14 +296,20 @@ __global__ void __launch_bounds__(64 * W) select_kernel(const double *__restrict
   const int wave = threadIdx.x >> 6;
   // phase 2's candidate buffers (64 keys and weights per wave) reuse the
   // pooled-row area, which phase 1's last barrier frees
-  uint64_t *cbuf = reinterpret_cast<uint64_t *>(sc + R * nB);
+  uint64_t *cbuf = reinterpret_cast<uint64_t *>(sc + R * NP);
 
   if constexpr (MASS) {
     const double *src = qbar + ((int64_t)bh * nB + r0) * nB;
-    for (int x = threadIdx.x; x < nr * nB; x += 64 * W) sc[x] = src[x];
+    for (int r = wave; r < nr; r += W)
+#pragma unroll
+      for (int u = 0; u < E; ++u) {
+        const int p = u * 64 + lane;
+        const double m = src[r * nB + min(p, nB - 1)];
+        sc[r * NP + p] = p < nB ? m : -INFINITY;
+      }
     __syncthreads();
   } else {
-    double *qs = sc + R * nB;
+    double *qs = sc + R * NP;
     {
       constexpr int SPT = R * D / (64 * W);  // staged values per thread (all loads in flight)
       double sv[SPT];
@@ -255,6 +324,8 @@ __global__ void __launch_bounds__(64 * W) select_kernel(const double *__restrict
         qs[r * QS + c] = sv[i];
       }
     }
+    for (int r = wave; r < nr; r += W)
+      for (int p = nB + lane; p < NP; p += 64) sc[r * NP + p] = -INFINITY;
     __syncthreads();
     {
       typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -264,36 +335,50 @@ __global__ void __launch_bounds__(64 * W) select_kernel(const double *__restrict
       // The groups start at a different place in every wave: walking them in
       // lockstep sends every wave of the chip to the same few L2 channels.
       const int rot = (wave * 5 + T * 3) & (NG - 1);
-      for (int j0 = wave * 16; j0 < nB; j0 += 16 * W) {
-        const double *kr = kb + (int64_t)min(j0 + li, nB - 1) * D + 4 * lk;
+      // All of a wave's first tile is loaded before its first product (left to
+      // itself the compiler keeps two loads in flight, and a tile then costs
+      // D / 8 L2 round trips instead of one); after that each channel group
+      // is loaded for the next tile as soon as its products are issued, so
+      // the loads of one tile run under the products of the other without a
+      // second set of registers.
+      double2 kv[NG][2];
+      const double *kr = kb + 4 * lk;
+      auto load = [&](int g, int j) __attribute__((always_inline)) {
+        const int gr = (g + rot) & (NG - 1);
+        const double *p = kr + (int64_t)min(j + li, nB - 1) * D + 16 * gr;
+        kv[g][0] = *reinterpret_cast<const double2 *>(p);
+        kv[g][1] = *reinterpret_cast<const double2 *>(p + 2);
+      };
+      auto tile = [&](auto next, int j0) __attribute__((always_inline)) {
         f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-        // All of the tile's loads are issued before the first product: left to
-        // itself the compiler keeps two in flight, and the tile then costs
-        // D / 8 L2 round trips instead of one.
-        double2 kv[NG][2];
-  #pragma unroll
-        for (int g = 0; g < NG; ++g) {
-          const int gr = (g + rot) & (NG - 1);
-          kv[g][0] = *reinterpret_cast<const double2 *>(kr + 16 * gr);
-          kv[g][1] = *reinterpret_cast<const double2 *>(kr + 16 * gr + 2);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-  #pragma unroll
+#pragma unroll
         for (int g = 0; g < NG; ++g) {
           const int gr = (g + rot) & (NG - 1);
           acc = __builtin_amdgcn_mfma_f64_16x16x4f64(qr[16 * gr + 0], kv[g][0].x, acc, 0, 0, 0);
           acc = __builtin_amdgcn_mfma_f64_16x16x4f64(qr[16 * gr + 1], kv[g][0].y, acc, 0, 0, 0);
           acc = __builtin_amdgcn_mfma_f64_16x16x4f64(qr[16 * gr + 2], kv[g][1].x, acc, 0, 0, 0);
           acc = __builtin_amdgcn_mfma_f64_16x16x4f64(qr[16 * gr + 3], kv[g][1].y, acc, 0, 0, 0);
+          if constexpr (decltype(next)::value) {
+            load(g, j0 + 16 * W);
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
         const int j = j0 + li;
         if (j < nB) {
-  #pragma unroll
+#pragma unroll
           for (int v = 0; v < 4; ++v) {
             const int r = lk + 4 * v;
-            if (r < nr) sc[r * nB + j] = sigma * acc[v];
+            if (r < nr) sc[r * NP + j] = sigma * acc[v];
           }
         }
+      };
+      int j0 = wave * 16;
+      if (j0 < nB) {
+#pragma unroll
+        for (int g = 0; g < NG; ++g) load(g, j0);
+        __builtin_amdgcn_sched_barrier(0);
+        for (; j0 + 16 * W < nB; j0 += 16 * W) tile(std::true_type{}, j0);
+        tile(std::false_type{}, j0);
       }
     }
     __syncthreads();
@@ -306,20 +391,25 @@ __global__ void __launch_bounds__(64 * W) select_kernel(const double *__restrict
   // The bisection state is the same in every lane and lives in scalar
   // registers; the vector work per step is one compare and add per position
   // and one wave sum.
+  const ExpCoef ec = exp_coef();
   for (int r = wave; r < nr; r += W) {
-    const double *row = sc + r * nB;
+    const double *row = sc + r * NP;
     const int64_t grow = (int64_t)bh * nB + r0 + r;
     double pl[E];
     uint64_t key[E];
     double smax = -INFINITY, smin = INFINITY;
+    // (positions below 64 EP are always valid: the launcher takes the
+    // smallest E with 64 E >= nB)
+    constexpr int EP = sel_prev(E);
+#pragma unroll
+    for (int u = 0; u < E; ++u) pl[u] = row[u * 64 + lane];  // the logit until the softmax below
 #pragma unroll
     for (int u = 0; u < E; ++u) {
       const int p = u * 64 + lane;
-      const bool ok = p < nB;
-      const double s = row[min(p, nB - 1)];
-      pl[u] = ok ? s : -INFINITY;  // the logit until the softmax below
+      const bool ok = u < EP || p < nB;
+      const double s = pl[u];
       key[u] = ok ? sel_key(s, p) : 0ull;  // valid keys are > 2047
-      smax = fmax(smax, pl[u]);
+      smax = fmax(smax, s);
       smin = ok ? fmin(smin, s) : smin;
     }
     smax = wave_max(smax);
@@ -329,27 +419,18 @@ __global__ void __launch_bounds__(64 * W) select_kernel(const double *__restrict
     double lsum = 0.0;
 #pragma unroll
     for (int u = 0; u < E; ++u) {
-      if constexpr (MASS) pl[u] = (u * 64 + lane < nB) ? pl[u] : 0.0;
-      else pl[u] = (u * 64 + lane < nB) ? exp(pl[u] - smax) : 0.0;
+      const bool ok = u < EP || u * 64 + lane < nB;
+      if constexpr (MASS) pl[u] = ok ? pl[u] : 0.0;
+      else pl[u] = ok ? exp_neg(pl[u] - smax, ec) : 0.0;
       lsum += pl[u];
     }
-    const double tauZ = tau * wave_sum(lsum);
+    const double Z = wave_sum(lsum);
+    const double tauZ = tau * Z;
 
-    // every key lies in [smallest key of value smin, largest key of smax]
-    Bisect bs{sel_key(smin, 2047), sel_key(smax, 0) + 1, 0, 0, 0.0, false, 0};
-    bool reach;
-    {
-      double m = 0.0;
-      int c = 0;
-#pragma unroll
-      for (int u = 0; u < E; ++u) {
-        const bool ge = key[u] >= bs.lo;
-        m += ge ? pl[u] : 0.0;
-        c += __popcll(__ballot(ge));
-      }
-      bs.cnt_lo = c;
-      reach = wave_sum(m) >= tauZ;
-    }
+    // every key lies in [smallest key of value smin, largest key of smax],
+    // and together they hold the whole mass Z
+    Bisect bs{sel_key(smin, 2047), sel_key(smax, 0) + 1, nB, 0, 0.0, false, 0};
+    const bool reach = Z >= tauZ;
     int k;
     double cut;
     if (!reach) {
@@ -399,35 +480,45 @@ __global__ void __launch_bounds__(64 * W) select_kernel(const double *__restrict
     }
     const double hiT = cut + kTieEps;
 
-    // |S+| : blocks strictly above the tie band
-    int nplus = 0;
+    // Lane u takes over chunk u (positions 64 u .. 64 u + 63) as two words:
+    // the blocks above the tie band (S+) and the tied ones.
+    uint64_t above = 0, tied = 0;
+    {
+      double sv[E];
 #pragma unroll
-    for (int u = 0; u < E; ++u) nplus += __popcll(__ballot(u * 64 + lane < nB && row[min(u * 64 + lane, nB - 1)] > hiT));
-    const int need = k - nplus;
-    // write the row in index order; the first `need` tied blocks are kept.
-    // As bits, the ballot of chunk u is word u of the row, stored by lane u.
-    int tied_before = 0;
-    uint64_t word = 0;
+      for (int u = 0; u < E; ++u) sv[u] = row[u * 64 + lane];
 #pragma unroll
-    for (int u = 0; u < E; ++u) {
-      const int jj = u * 64 + lane;
-      const bool ok = jj < nB;
-      const double sv = row[min(jj, nB - 1)];
-      const bool above = ok && sv > hiT;
-      const bool tie = ok && fabs(sv - cut) <= kTieEps;
-      const unsigned long long tb = __ballot(tie);
-      const int rank = tied_before + __popcll(tb & ((1ull << lane) - 1ull));
-      const bool keep = above || (tie && rank < need);
-      if (bits == nullptr) {
-        if (ok) mask[grow * nB + jj] = keep ? 1 : 0;
-      } else {
-        const uint64_t kw = __ballot(keep);
-        word = lane == u ? kw : word;
+      for (int u = 0; u < E; ++u) {
+        const bool ok = u < EP || u * 64 + lane < nB;
+        const uint64_t a = __ballot(ok && sv[u] > hiT);
+        const uint64_t t = __ballot(ok && fabs(sv[u] - cut) <= kTieEps);
+        above = lane == u ? a : above;
+        tied = lane == u ? t : tied;
       }
-      tied_before += __popcll(tb);
     }
-    const int nw = (nB + 63) / 64;
-    if (bits != nullptr && lane < nw) bits[grow * nw + lane] = word;
+    // the first `need` tied blocks in index order are kept
+    const int need = k - wave_sum_i32(__popcll(above));
+    const int nt = __popcll(tied);
+    int left = min(max(need - (wave_incl_scan(nt) - nt), 0), nt);  // of this chunk
+    uint64_t word = above | (left == nt ? tied : 0ull);
+    if (left < nt)
+      for (; left > 0; --left) {
+        word |= tied & (0ull - tied);
+        tied &= tied - 1ull;
+      }
+    // write the row: word u from lane u, or as bytes, chunk by chunk
+    if (bits != nullptr) {
+      const int nw = (nB + 63) / 64;
+      if (lane < nw) bits[grow * nw + lane] = word;
+    } else {
+      uint8_t *mrow = mask + grow * nB;
+#pragma unroll
+      for (int u = 0; u < E; ++u) {
+        const uint64_t w = read_lane(word, u);
+        const int jj = u * 64 + lane;
+        if (u < EP || jj < nB) mrow[jj] = (uint8_t)((w >> lane) & 1ull);
+      }
+    }
   }
 }
 
@@ -456,55 +547,52 @@ static hipError_t launch_select_dr(const double *qbar, const double *kbar, int B
   const int G = (nB + R - 1) / R * BH;
   dim3 grid((G + 7) / 8 * 8);
   // the logits, then the pooled rows or phase 2's candidate buffers
-  const size_t lds = ((size_t)R * nB + (size_t)max(R * (D + 2), W * 128)) * sizeof(double);
   const int need = (nB + 63) / 64;  // positions per lane
+  // the logits (rows padded to 64 E), then the pooled rows or phase 2's
+  // candidate buffers
+  const auto lds_of = [](int e) { return ((size_t)R * 64 * e + (size_t)max(R * (D + 2), W * 128)) * sizeof(double); };
 #define CARNATOR_SEL(EE)                                                                          \
   do {                                                                                            \
+    const size_t lds = lds_of(EE);                                                                \
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&select_kernel<D, EE, R, W, MASS>), \
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);     \
     if (e != hipSuccess) return e;                                                                \
     hipLaunchKernelGGL((select_kernel<D, EE, R, W, MASS>), grid, dim3(64 * W), lds, s, qbar, kbar, nB, \
                        sigma, tau, mask, bits, BH);                                               \
   } while (0)
-  // W = 16 waves (1024 threads, at most 128 VGPRs) only while a lane holds at
-  // most 8 positions; the launcher picks R and W accordingly
-  if (need <= 1) CARNATOR_SEL(1);
-  else if (need <= 2) CARNATOR_SEL(2);
-  else if (need <= 3) CARNATOR_SEL(3);
-  else if (need <= 4) CARNATOR_SEL(4);
-  else if (need <= 6) CARNATOR_SEL(6);
-  else if (need <= 8) CARNATOR_SEL(8);
-  else if constexpr (W <= 8) {
-    if (need <= 10) CARNATOR_SEL(10);
+  if constexpr (R == 16) {  // serves nB <= 1024
+    if (need <= 1) CARNATOR_SEL(1);
+    else if (need <= 2) CARNATOR_SEL(2);
+    else if (need <= 3) CARNATOR_SEL(3);
+    else if (need <= 4) CARNATOR_SEL(4);
+    else if (need <= 6) CARNATOR_SEL(6);
+    else if (need <= 8) CARNATOR_SEL(8);
+    else if (need <= 10) CARNATOR_SEL(10);
     else if (need <= 12) CARNATOR_SEL(12);
     else if (need <= 16) CARNATOR_SEL(16);
-    else if constexpr (R <= 8) {  // R = 16 serves nB <= 1024 only
-      if (need <= 24) CARNATOR_SEL(24);
-      else if (need <= 32) CARNATOR_SEL(32);
-      else return hipErrorInvalidValue;
-    } else {
-      return hipErrorInvalidValue;
-    }
-  } else {
-    return hipErrorInvalidValue;
+    else return hipErrorInvalidValue;
+  } else {  // longer rows
+    if (need <= 24) CARNATOR_SEL(24);
+    else if (need <= 32) CARNATOR_SEL(32);
+    else return hipErrorInvalidValue;
   }
 #undef CARNATOR_SEL
   return hipGetLastError();
 }
 
-// R query blocks per workgroup: their logits and pooled rows (or the
-// selection's candidate buffers, 1 KiB per wave) take 8 (R nB + max(R (d + 2),
-// 128 W)) bytes of LDS, within 160 KiB for R = 16 up to nB = 1024 and for
-// R = 8 up to nB = 2048.  R = 16 fills the 16-row fp64 MFMA tiles
-// and halves the kbar re-reads.  W = 16 waves (one row each) while a lane's
-// share of a row (E <= 8 positions) fits the 128 registers of a 1024-thread
-// workgroup, else W = 8 (two rows each when R = 16).
+// R query blocks per workgroup: their logits (rows padded to 64 E) and pooled
+// rows (or the selection's candidate buffers, 1 KiB per wave) take
+// 8 (64 E R + max(R (d + 2), 128 W)) bytes of LDS, within 160 KiB for R = 16 up
+// to nB = 1024 and for R = 8 up to nB = 2048.  R = 16 fills the 16-row fp64
+// MFMA tiles and halves the kbar re-reads; W = R waves, one row each: with one
+// workgroup per CU (its LDS) the waves of that workgroup are all there is to
+// hide the phases' latencies (at nB = 591 244 us with 8 waves of two rows
+// each, 215 us with 16 waves).
 template <int D>
 static hipError_t launch_select_d(const double *qbar, const double *kbar, int BH, int nB,
                                   double sigma, double tau, uint8_t *mask, uint64_t *bits,
                                   hipStream_t s) {
-  if (nB <= 512) return launch_select_dr<D, 16, 16, false>(qbar, kbar, BH, nB, sigma, tau, mask, bits, s);
-  if (nB <= 1024) return launch_select_dr<D, 16, 8, false>(qbar, kbar, BH, nB, sigma, tau, mask, bits, s);
+  if (nB <= 1024) return launch_select_dr<D, 16, 16, false>(qbar, kbar, BH, nB, sigma, tau, mask, bits, s);
   return launch_select_dr<D, 8, 8, false>(qbar, kbar, BH, nB, sigma, tau, mask, bits, s);
 }
 
@@ -518,8 +606,7 @@ hipError_t launch_select(const double *qbar, const double *kbar, int BH, int nB,
 hipError_t launch_select_mass(const double *mass, int BH, int nB, double tau, uint8_t *mask,
                               uint64_t *bits, hipStream_t s) {
   // the pooled-row area of the LDS layout is not used: the smallest D
-  if (nB <= 512) return launch_select_dr<64, 16, 16, true>(mass, nullptr, BH, nB, 1.0, tau, mask, bits, s);
-  if (nB <= 1024) return launch_select_dr<64, 16, 8, true>(mass, nullptr, BH, nB, 1.0, tau, mask, bits, s);
+  if (nB <= 1024) return launch_select_dr<64, 16, 16, true>(mass, nullptr, BH, nB, 1.0, tau, mask, bits, s);
   return launch_select_dr<64, 8, 8, true>(mass, nullptr, BH, nB, 1.0, tau, mask, bits, s);
 }
 
