@@ -8,21 +8,38 @@
 //   M[b,h,i,j] = (1 / n_i) sum_{a in block i} sum_{t in block j}
 //                softmax_t(sigma q_a . k_t)        (rows sum to 1)
 //
-// Pass 1 (mass_pass_kernel): one workgroup of 8 waves per 512 queries (four
-// blocks of 128 or eight of 64), 64 queries per wave in two sets of 32 (each
-// K operand read from LDS feeds two MFMAs), streams every key block of its
-// head through LDS (each load serves 512 queries) and computes
-// S^T = K Q^T on bf16 MFMA 32x32x16 (fp32 accumulation), keys as MFMA rows so
-// that a query's scores sit in one lane pair.  After key block j each query
-// records (m_j, s_j): its running maximum (log2 units) and the block's
-// sum of 2^(x - m_j); at the end its log2-sum-exp L.  Pass 2
-// (mass_reduce_kernel) forms M_ij = sum_a s_j 2^(m_j - L) / n_i (the powers in
-// fp32, the sum in fp64).
-// The records are block-major ([bh][j][a]) so a wave's 32 queries write 256
+// Pass 1 (mass_pass_kernel): a workgroup of NW waves per 64 NW queries, 64
+// queries per wave in two sets of 32, streams every key block of its head
+// through LDS and computes S^T = K Q^T on bf16 MFMA 32x32x16 (fp32
+// accumulation), keys as MFMA rows so that a query's scores sit in one lane
+// pair.  Each query has one reference r (log2 units, a whole number, fixed
+// for the whole pass), and per key block one fp32 record s_j = sum of
+// 2^(x - r) over the block's keys; at the end its total l (fp64).  Pass 2
+// (mass_reduce_kernel) forms M_ij = sum_a s_j / l_a / n_i in fp64.
+// The records are block-major ([bh][j][a]) so a wave's 64 queries write 256
 // contiguous bytes.
+//
+// The reference is the maximum over the query's first 32 keys, at least 0: no
+// running maximum and no rescaling, a score costs one fma, one exp2 and one
+// add.  2^(x - r) spans 2^-126 .. 2^127 whatever r is, so the sums are as
+// precise as with the row maximum; with r >= 0 the fma rounds x - r no
+// coarser than x itself for every x that carries mass.  A query whose total
+// leaves [2^-40, 2^100] (scores more than 100 log2 units above its first
+// keys, or all below -40) makes its workgroup start over with the true row
+// maxima, taken in a pass of their own.
+//
+// Bound: the vector work beside the MFMAs (per 32-key tile and set D / 16
+// MFMAs against 16 fma, 16 exp2 and 16 adds).  12 heads of 32,760 tokens, d =
+// 128: both passes 2.95 ms, 1120 TFLOP/s (3.56 ms with the MFMAs and then the
+// exponentials of a tile in turn, a running maximum and 8-byte records); 48
+// heads of 17,776 tokens, d = 64: 2.33 ms (3.34).  Relative error of the
+// masses against 64 bits 2e-8 .. 4e-8 (7e-8 .. 2e-7 with log2-sum-exps).
 #include "internal.h"
 
+#include <math.h>
+
 #include <algorithm>
+#include <type_traits>
 
 namespace carnator {
 namespace {
@@ -38,204 +55,241 @@ __device__ inline int mswz(int r) {
   else return (r >> 1) & 7;
 }
 
-constexpr int kMassWaves = 8;  // 64 queries per wave, 512 per workgroup
-constexpr int kMassQueries = 64 * kMassWaves;
+// 16 bytes per lane from p to LDS offset lds_off + 16 lane (lds_off the same
+// in every lane): a direct load, inline so that the compiler does not drain
+// it before the next LDS read.  M0 is written a wait state before its use.
+__device__ inline void mass_dma16(const void *p, unsigned lds_off) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(p),
+               "s"(__builtin_amdgcn_readfirstlane(lds_off))
+               : "memory", "m0");
+}
+__device__ inline void mass_wait_barrier() {
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+__device__ inline void mass_anchor(float x) { asm volatile("" ::"v"(x)); }
 
-// Softmax statistics of one query (pair-uniform): the running maximum and
-// sum over the key blocks done, and the current block's maximum and this
-// lane's share of its sum.
-struct MassState {
-  float m_run, l_run, mb, sl;
-};
-
-// Fold one 32-key tile of scores (raw; with MASK, keys at or past lim
-// masked: only the last key block can be partial) into st.
-template <bool MASK>
-__device__ __attribute__((always_inline)) inline void mass_tile(MassState &st, f32x16 acc, int m,
-                                                                int hh, int lim, float c2) {
-  float tm = -INFINITY;
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    if constexpr (MASK) {
-      const int key = m * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
-      acc[v] = key < lim ? acc[v] : -INFINITY;
-    }
-    tm = fmaxf(tm, acc[v]);
-  }
-  tm = fmaxf(tm, __shfl_xor(tm, 32)) * c2;
-  const float mn = fmaxf(st.mb, tm);
-  float ts = 0.f;
-#pragma unroll
-  for (int v = 0; v < 16; ++v) ts += __builtin_amdgcn_exp2f(fmaf(acc[v], c2, -mn));
-  st.sl = st.sl * __builtin_amdgcn_exp2f(st.mb == -INFINITY ? -INFINITY : st.mb - mn) + ts;
-  st.mb = mn;
+// x of the lane pair (l, l + 32), combined in the same order in both lanes.
+__device__ inline float pair_max(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+// Lanes 0 .. 31: the pair sum of a, lanes 32 .. 63: that of b.
+__device__ inline float pair_sums(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// One 32-key tile of S^T = K Q^T for both query sets: each K operand (row r
-// of the tile for this lane, chunks 2 t + hh, from LDS) feeds two MFMAs.
-template <int D, int CPR>
-__device__ __attribute__((always_inline)) inline void qk_tile2(const unsigned char *row, int r,
-                                                                int hh, const bf16x8 (&q0)[D / 16],
-                                                                const bf16x8 (&q1)[D / 16],
-                                                                f32x16 &acc0, f32x16 &acc1) {
-  acc0 = f32x16{};
-  acc1 = f32x16{};
-#pragma unroll
-  for (int t = 0; t < D / 16; ++t) {
-    const int c = 2 * t + hh;
-    const bf16x8 kv = *reinterpret_cast<const bf16x8 *>(row + 16 * (c ^ mswz<CPR>(r)));
-    acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kv, q0[t], acc0, 0, 0, 0);
-    acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kv, q1[t], acc1, 0, 0, 0);
-  }
-}
-
-template <int D, int BS>
+template <int D, int BS, int NW>
 struct MassCfg {
-  static constexpr int QPW = kMassQueries / BS;  // query blocks per workgroup
-  static constexpr int NT = 64 * kMassWaves;
-  static constexpr int CPR = D / 8;        // 16-byte chunks per K row
-  static constexpr int RB = D * 2;         // bytes per K row
-  static constexpr int TILE = BS * RB;     // one key block in LDS
-  static constexpr int LDS = 2 * TILE;     // double buffer
-  static constexpr int CPT = BS * CPR / NT;  // chunks loaded per thread per block
-  static_assert(BS * CPR % NT == 0, "chunk split");
+  static constexpr int NT = 64 * NW;
+  static constexpr int Q = 64 * NW;          // queries per workgroup
+  static constexpr int CPR = D / 8;          // 16-byte chunks per K row
+  static constexpr int RB = D * 2;           // bytes per K row
+  static constexpr int TILE = BS * RB;       // one key block in LDS
+  static constexpr int LDS = 2 * TILE;       // double buffer
+  static constexpr int RPL = 1024 / RB;      // rows per 1-KiB direct load
+  static constexpr int LI = TILE / 1024 / NW;  // direct loads per wave per block
+  static constexpr int F = D / 16;           // K fragments (MFMA steps) per tile
+  static constexpr int MT = BS / 32;         // tiles per block
+  static_assert(TILE % (1024 * NW) == 0 && 16 % F == 0, "tile split");
 };
 
-template <int D, int BS>
-__global__ void __launch_bounds__(64 * kMassWaves)
+// One 32-key tile and query set at a time: MFMA step t of one set shares its
+// slot with 16 / F scores of the other set's exponentials, so every wave's
+// instruction stream keeps both units busy.  Per block and tile m:
+//   Y: accB = K(m) Q_B^T   beside the exponentials of accA (tile m); each K
+//      fragment is refilled with tile m + 1 once used for the last time
+//   X: accA = K(m + 1) Q_A^T beside the exponentials of accB (tile m)
+// The tile after a block's last is the next block's first.  The barrier
+// before a block's last Y says that the next block is in LDS and that nobody
+// reads this block's tile any more; the block after the next is then loaded
+// into it.
+//
+// At d = 64 with 8 waves the kernel is held to 128 registers (a few spills
+// outside the loop), so that two workgroups share a CU: the exponentials take
+// twice the MFMAs' time there, and four waves per SIMD fill their latencies
+// better than two (2.33 against 2.47 ms on 48 heads of 17,776 tokens).
+template <int D, int BS, int NW>
+__global__ void __launch_bounds__(64 * NW, (D == 64 && NW == 8) ? 4 : 2)
 mass_pass_kernel(View q, View k, int H, int N, int nB, int bh0, float c2,
-                 float2 *__restrict__ rec, float *__restrict__ lse2) {
-  using C = MassCfg<D, BS>;
+                 float *__restrict__ rec, float *__restrict__ total) {
+  using C = MassCfg<D, BS, NW>;
+  constexpr int F = C::F, MT = C::MT, SPS = 16 / F;
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
-  const int ng = (nB + C::QPW - 1) / C::QPW;  // query groups per head
+  const int ng = (nB * BS + C::Q - 1) / C::Q;  // query groups per head
   const int qg = (int)(blockIdx.x % ng);
-  // heads bh0 .. of the chunk this launch covers; records and log2-sum-exps
-  // are indexed inside the chunk
+  // heads bh0 .. of the chunk this launch covers; records and totals are
+  // indexed inside the chunk
   const int bc = (int)(blockIdx.x / ng);
   const int bh = bh0 + bc;
   const int b = bh / H, h = bh - b * H;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
-  // this lane's two queries: l32 of each of the wave's two sets of 32
-  const int a0 = qg * kMassQueries + wave * 64 + l32, a1 = a0 + 32;
-  const bool qv0 = a0 < N, qv1 = a1 < N;
+  // the scores of this lane belong to query l32 of each of the wave's two
+  // sets of 32; its records to query `lane` of the 64
+  const int aw = qg * C::Q + wave * 64;
+  const bool mine = aw + lane < N;
 
   // Q as the B operand: query l32 of a set, channels 16 t + 8 hh .. + 8
-  bf16x8 q0[D / 16], q1[D / 16];
+  bf16x8 q0[F], q1[F];
   {
-    const uint16_t *qh = q.data + (int64_t)b * q.sb + (int64_t)h * q.sh;
+    const uint16_t *qh = q.data + (int64_t)b * q.sb + (int64_t)h * q.sh + 8 * hh;
+    const int a0 = aw + l32, a1 = a0 + 32;
     const uint16_t *p0 = qh + (int64_t)min(a0, N - 1) * q.sn;
     const uint16_t *p1 = qh + (int64_t)min(a1, N - 1) * q.sn;
 #pragma unroll
-    for (int t = 0; t < D / 16; ++t) {
-      const uint4 v0 = *reinterpret_cast<const uint4 *>(p0 + 16 * t + 8 * hh);
-      const uint4 v1 = *reinterpret_cast<const uint4 *>(p1 + 16 * t + 8 * hh);
-      q0[t] = qv0 ? __builtin_bit_cast(bf16x8, v0) : bf16x8{};
-      q1[t] = qv1 ? __builtin_bit_cast(bf16x8, v1) : bf16x8{};
+    for (int t = 0; t < F; ++t) {
+      const uint4 v0 = *reinterpret_cast<const uint4 *>(p0 + 16 * t);
+      const uint4 v1 = *reinterpret_cast<const uint4 *>(p1 + 16 * t);
+      q0[t] = a0 < N ? __builtin_bit_cast(bf16x8, v0) : bf16x8{};
+      q1[t] = a1 < N ? __builtin_bit_cast(bf16x8, v1) : bf16x8{};
     }
   }
+  // the fragments are in registers before any direct load is issued
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+
+  // Direct loads: the i-th of this wave fills rows RPL (wave LI + i) .. + RPL
+  // of a block's tile; lane l writes 16 bytes at 16 l, slot `slot` of row
+  // +lrow, which holds chunk slot ^ swz(row).  Rows past N read row N - 1.
   const uint16_t *kbase = k.data + (int64_t)b * k.sb + (int64_t)h * k.sh;
+  const int lrow = lane / (C::RB / 16), slot = lane % (C::RB / 16);
+  const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char *)lds;
+  auto load_block = [&](int j, int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < C::LI; ++i) {
+      const int r = C::RPL * (wave * C::LI + i) + lrow;
+      const int tok = min(j * BS + r, N - 1);
+      mass_dma16(kbase + (int64_t)tok * k.sn + (slot ^ mswz<C::CPR>(r)) * 8,
+                 lds_base + (unsigned)(buf * C::TILE + (wave * C::LI + i) * 1024));
+    }
+  };
+  // K fragment t of a tile (A operand): row l32, chunk 2 t + hh
+  int kread[F];
+  auto reset_kread = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < F; ++t) kread[t] = l32 * C::RB + 16 * ((2 * t + hh) ^ mswz<C::CPR>(l32));
+  };
+  bf16x8 kf[F];
+  auto frag = [&](int t, int m) __attribute__((always_inline)) {
+    kf[t] = *reinterpret_cast<const bf16x8 *>(lds + kread[t] + m * 32 * C::RB);
+  };
+  auto mfma = [&](f32x16 &acc, const bf16x8 (&qf)[F], int t) __attribute__((always_inline)) {
+    if (t == 0) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t], qf[t], f32x16{}, 0, 0, 0);
+    else acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t], qf[t], acc, 0, 0, 0);
+  };
+  auto tile_max = [&](const f32x16 &acc) __attribute__((always_inline)) {
+    float m = acc[0];
+#pragma unroll
+    for (int v = 1; v < 16; ++v) m = fmaxf(m, acc[v]);
+    return pair_max(m);
+  };
 
-  // staged chunks of a key block: chunk x = tid + u NT covers row x / CPR,
-  // 16-byte chunk x % CPR (rows past N read row N - 1, blocks past nB - 1
-  // block nB - 1; their scores are masked or unused).
-  // Two register stages: the load of key block j + 2 is issued right after
-  // block j + 1 is stored to LDS, so it has two blocks of compute to land.
-  // The loop is unrolled by two so both stage arrays stay in registers, and
-  // runs an even number of bodies (an odd nB ends with one masked body over
-  // the LDS buffer it finds: nothing is recorded from it).
-  // (named registers, not arrays: arrays live across the loop's back edge
-  // were kept in scratch memory, each prefetch then waited for at once)
-  static_assert(C::CPT <= 4, "stage size");
-  uint4 sa0, sa1, sa2, sa3, sb0, sb1, sb2, sb3;
-#define CARNATOR_MASS_CHUNK_LOAD(V, U, J)                                                \
-  if constexpr ((U) < C::CPT) {                                                          \
-    const int x = (int)threadIdx.x + (U) * C::NT;                                        \
-    const int r = x / C::CPR, c = x - r * C::CPR;                                        \
-    const int tok = min(min(J, nB - 1) * BS + r, N - 1);                                 \
-    V = *reinterpret_cast<const uint4 *>(kbase + (int64_t)tok * k.sn + 8 * c);           \
+  f32x16 accA, accB;
+  float refA = 0.f, refB = 0.f;
+  double l = 0.0;
+  // at most two rounds: the second with the row maxima as references
+  for (int round = 0; round < 2; ++round) {
+    reset_kread();
+    if (round == 1) {
+      float mA = -INFINITY, mB = -INFINITY;
+      for (int j = 0; j < nB; ++j) {
+        load_block(j, 0);
+        mass_wait_barrier();
+        for (int m = 0; m < MT; ++m) {
+#pragma unroll
+          for (int t = 0; t < F; ++t) frag(t, m);
+#pragma unroll
+          for (int t = 0; t < F; ++t) mfma(accA, q0, t), mfma(accB, q1, t);
+          mA = fmaxf(mA, tile_max(accA));
+          mB = fmaxf(mB, tile_max(accB));
+        }
+        mass_wait_barrier();
+      }
+      refA = ceilf(mA * c2), refB = ceilf(mB * c2);
+    }
+    load_block(0, 0);
+    load_block(min(1, nB - 1), 1);
+    mass_wait_barrier();
+#pragma unroll
+    for (int t = 0; t < F; ++t) frag(t, 0);
+#pragma unroll
+    for (int t = 0; t < F; ++t) mfma(accA, q0, t), mfma(accB, q1, t);
+    if (round == 0) {
+      refA = fmaxf(ceilf(tile_max(accA) * c2), 0.f);
+      refB = fmaxf(ceilf(tile_max(accB) * c2), 0.f);
+    }
+    l = 0.0;
+    float psA0, psA1, psB0, psB1;
+    // scores [v, v + SPS) of a tile
+    auto expo = [&](const f32x16 &acc, float ref, float &s0, float &s1, int v, int key0, int lim,
+                    auto masked) __attribute__((always_inline)) {
+#pragma unroll
+      for (int x = v; x < v + SPS; x += 2) {
+        float e0 = __builtin_amdgcn_exp2f(fmaf(acc[x], c2, -ref));
+        float e1 = __builtin_amdgcn_exp2f(fmaf(acc[x + 1], c2, -ref));
+        if constexpr (decltype(masked)::value) {
+          int left = lim - key0 - 4 * hh;
+          asm volatile("" : "+v"(left));  // compared here, not 64 times ahead of the loop
+          e0 = 8 * (x >> 2) + (x & 3) < left ? e0 : 0.f;
+          e1 = 8 * (x >> 2) + (x & 3) + 1 < left ? e1 : 0.f;
+        }
+        s0 += e0;
+        s1 += e1;
+        mass_anchor(s0);
+        mass_anchor(s1);
+      }
+    };
+    auto block = [&](auto masked, int j) __attribute__((always_inline)) {
+      psA0 = psA1 = psB0 = psB1 = 0.f;
+      const int lim = N - j * BS;  // valid keys of this block (used when masked)
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        if (m == MT - 1) {
+          mass_wait_barrier();
+          if (j + 2 < nB) load_block(j + 2, j & 1);
+        }
+        // Y
+#pragma unroll
+        for (int t = 0; t < F; ++t) {
+          mfma(accB, q1, t);
+          if (m < MT - 1) {
+            frag(t, m + 1);
+          } else {
+            kread[t] ^= C::TILE;
+            frag(t, 0);
+          }
+          expo(accA, refA, psA0, psA1, t * SPS, 32 * m, lim, masked);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        // X
+#pragma unroll
+        for (int t = 0; t < F; ++t) {
+          mfma(accA, q0, t);
+          expo(accB, refB, psB0, psB1, t * SPS, 32 * m, lim, masked);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      const float s = pair_sums(psA0 + psA1, psB0 + psB1);
+      l += (double)s;
+      if (mine) rec[((int64_t)bc * nB + j) * N + aw + lane] = s;
+    };
+    for (int j = 0; j < nB - 1; ++j) block(std::false_type{}, j);
+    block(std::true_type{}, nB - 1);  // only the last block can be partial
+    const bool bad = mine && !(l >= 0x1p-40 && l <= 0x1p100);
+    if (round == 1 || !__syncthreads_or(bad)) break;
   }
-#define CARNATOR_MASS_CHUNK_STORE(V, U, BUF)                                             \
-  if constexpr ((U) < C::CPT) {                                                          \
-    const int x = (int)threadIdx.x + (U) * C::NT;                                        \
-    const int r = x / C::CPR, c = x - r * C::CPR;                                        \
-    *reinterpret_cast<uint4 *>(lds + (BUF) * C::TILE + r * C::RB +                       \
-                               16 * (c ^ mswz<C::CPR>(r))) = V;                          \
-  }
-#define CARNATOR_MASS_LOAD(ST, J)                                                        \
-  CARNATOR_MASS_CHUNK_LOAD(ST##0, 0, J) CARNATOR_MASS_CHUNK_LOAD(ST##1, 1, J)            \
-  CARNATOR_MASS_CHUNK_LOAD(ST##2, 2, J) CARNATOR_MASS_CHUNK_LOAD(ST##3, 3, J)
-#define CARNATOR_MASS_STORE(ST, BUF)                                                     \
-  CARNATOR_MASS_CHUNK_STORE(ST##0, 0, BUF) CARNATOR_MASS_CHUNK_STORE(ST##1, 1, BUF)      \
-  CARNATOR_MASS_CHUNK_STORE(ST##2, 2, BUF) CARNATOR_MASS_CHUNK_STORE(ST##3, 3, BUF)
-
-  CARNATOR_MASS_LOAD(sa, 0)
-  CARNATOR_MASS_STORE(sa, 0)
-  CARNATOR_MASS_LOAD(sa, 1)
-  CARNATOR_MASS_LOAD(sb, 2)
-  __syncthreads();
-
-  MassState s0 = {-INFINITY, 0.f, -INFINITY, 0.f}, s1 = s0;
-  // one key block: LDS buffer jj & 1 holds block jj, S1 holds block jj + 1
-  // and S2 block jj + 2 (both in flight); S1 is stored for the next body and
-  // refilled with block jj + 3
-#define CARNATOR_MASS_BODY(JJ, S1, MASK)                                                 \
-  {                                                                                      \
-    const int jj = (JJ);                                                                 \
-    const bool live = jj < nB;                                                           \
-    const unsigned char *base = lds + (jj & 1) * C::TILE;                                \
-    const int lim = N - jj * BS;                                                         \
-    s0.mb = s0.m_run, s0.sl = 0.f, s1.mb = s1.m_run, s1.sl = 0.f;                        \
-    _Pragma("unroll") for (int m = 0; m < BS / 32; ++m) {                                \
-      const int r = m * 32 + l32;                                                        \
-      f32x16 acc0, acc1;                                                                 \
-      qk_tile2<D, C::CPR>(base + r * C::RB, r, hh, q0, q1, acc0, acc1);                  \
-      mass_tile<MASK>(s0, acc0, m, hh, lim, c2);                                         \
-      mass_tile<MASK>(s1, acc1, m, hh, lim, c2);                                         \
-    }                                                                                    \
-    const float t0 = s0.sl + __shfl_xor(s0.sl, 32), t1 = s1.sl + __shfl_xor(s1.sl, 32);  \
-    if (live) {                                                                          \
-      s0.l_run = s0.l_run * __builtin_amdgcn_exp2f(s0.m_run == -INFINITY ? -INFINITY : s0.m_run - s0.mb) + t0; \
-      s0.m_run = s0.mb;                                                                  \
-      s1.l_run = s1.l_run * __builtin_amdgcn_exp2f(s1.m_run == -INFINITY ? -INFINITY : s1.m_run - s1.mb) + t1; \
-      s1.m_run = s1.mb;                                                                  \
-      float2 *rj = rec + ((int64_t)bc * nB + jj) * N;                                    \
-      if (hh == 0 && qv0) rj[a0] = make_float2(s0.mb, t0);                               \
-      if (hh == 0 && qv1) rj[a1] = make_float2(s1.mb, t1);                               \
-    }                                                                                    \
-    CARNATOR_MASS_STORE(S1, (jj + 1) & 1)                                                \
-    __syncthreads();                                                                     \
-    CARNATOR_MASS_LOAD(S1, jj + 3)                                                       \
-  }
-
-  // every key block but the last is full: the pairs before the one holding
-  // block nB - 1 take no key mask
-  const int jl = (nB - 1) & ~1;
-  for (int j = 0; j < jl; j += 2) {
-    CARNATOR_MASS_BODY(j, sa, false)
-    CARNATOR_MASS_BODY(j + 1, sb, false)
-  }
-  CARNATOR_MASS_BODY(jl, sa, true)
-  CARNATOR_MASS_BODY(jl + 1, sb, true)
-#undef CARNATOR_MASS_BODY
-#undef CARNATOR_MASS_LOAD
-#undef CARNATOR_MASS_STORE
-#undef CARNATOR_MASS_CHUNK_LOAD
-#undef CARNATOR_MASS_CHUNK_STORE
-  if (hh == 0 && qv0) lse2[(int64_t)bc * N + a0] = s0.m_run + log2f(s0.l_run);
-  if (hh == 0 && qv1) lse2[(int64_t)bc * N + a1] = s1.m_run + log2f(s1.l_run);
+  if (mine) total[(int64_t)bc * N + aw + lane] = (float)l;
 }
 
-// One wave per (bh, i): lane l holds queries a0 + l and a0 + 64 + l of block
-// i (the valid ones among them) and their L; the wave walks the key blocks
-// j, eight at a time with all their record loads in flight, and forms
-// M_ij = sum_a s 2^(m - L_a) / n_i with one wave sum per j.  2^(m - L) is
-// taken in fp32 (m <= L, both fp32 log2 values; relative error ~1e-6) and
-// the terms are summed in fp64.
+// One wave per (bh, i): lane x holds queries a0 + x and a0 + 64 + x of block
+// i (the valid ones among them) and the reciprocals of their totals; the
+// wave walks the key blocks j, eight at a time with all their record loads
+// in flight, and forms M_ij = sum_a s / l_a / n_i in fp64 with one wave sum
+// per j.
 constexpr int kReduceUnroll = 8;
-__global__ void __launch_bounds__(256) mass_reduce_kernel(const float2 *__restrict__ rec,
-                                                          const float *__restrict__ lse2, int N,
+__global__ void __launch_bounds__(256) mass_reduce_kernel(const float *__restrict__ rec,
+                                                          const float *__restrict__ total, int N,
                                                           int nB, int bs, int rows,
                                                           double *__restrict__ mass) {
   const int w = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
@@ -244,41 +298,41 @@ __global__ void __launch_bounds__(256) mass_reduce_kernel(const float2 *__restri
   const int i = w % nB, bh = w / nB;
   const int a0 = i * bs, a1 = min(a0 + bs, N);
   const int qa = a0 + lane, qb = a0 + 64 + lane;
-  const bool va = qa < a1, vb = qb < a1;
   const int ca = min(qa, N - 1), cb = min(qb, N - 1);  // clamped: loads stay in the head
-  const float *lh = lse2 + (int64_t)bh * N;
-  const float La = lh[ca], Lb = lh[cb];
-  const float2 *rh = rec + (int64_t)bh * nB * N;
+  const float *lh = total + (int64_t)bh * N;
   const double inv = 1.0 / (double)(a1 - a0);
+  const bool va = qa < a1, vb = qb < a1;
+  const double wa = inv / (double)lh[ca], wb = inv / (double)lh[cb];
+  const float *rh = rec + (int64_t)bh * nB * N;
   double *out = mass + (int64_t)w * nB;
   for (int j0 = 0; j0 < nB; j0 += kReduceUnroll) {
-    float2 ra[kReduceUnroll], rb[kReduceUnroll];
+    float ra[kReduceUnroll], rb[kReduceUnroll];
 #pragma unroll
     for (int u = 0; u < kReduceUnroll; ++u) {
-      const float2 *rj = rh + (int64_t)min(j0 + u, nB - 1) * N;
+      const float *rj = rh + (int64_t)min(j0 + u, nB - 1) * N;
       ra[u] = rj[ca];
       rb[u] = rj[cb];
     }
 #pragma unroll
     for (int u = 0; u < kReduceUnroll; ++u) {
-      double t = va ? (double)(ra[u].y * __builtin_amdgcn_exp2f(ra[u].x - La)) : 0.0;
-      t += vb ? (double)(rb[u].y * __builtin_amdgcn_exp2f(rb[u].x - Lb)) : 0.0;
+      double t = va ? (double)ra[u] * wa : 0.0;
+      t += vb ? (double)rb[u] * wb : 0.0;
       t = wave_sum(t);
-      if (lane == 0 && j0 + u < nB) out[j0 + u] = t * inv;
+      if (lane == 0 && j0 + u < nB) out[j0 + u] = t;
     }
   }
 }
 
 }  // namespace
 
-// The records take 8 bytes per (query, key block) of a head: 67 MB at 32K
-// tokens, 887 MB at 119K.  Heads are processed in chunks whose records fit
+// The records take 4 bytes per (query, key block) of a head: 34 MB at 32K
+// tokens, 443 MB at 119K.  Heads are processed in chunks whose records fit
 // in kMassScratchCap (at least one head per chunk), so the workspace stays
 // bounded whatever the number of heads.
 constexpr size_t kMassScratchCap = (size_t)4 << 30;
 
 static size_t mass_head_bytes(int N, int nB) {
-  return (size_t)nB * N * sizeof(float2) + (size_t)N * sizeof(float);
+  return ((size_t)nB + 1) * N * sizeof(float);
 }
 
 static int mass_chunk_heads(int BH, int N, int nB) {
@@ -287,9 +341,28 @@ static int mass_chunk_heads(int BH, int N, int nB) {
   return (int)std::max<size_t>(1, std::min<size_t>(fit, (size_t)BH));
 }
 
+// Whether the pass takes workgroups of 4 waves (256 queries) instead of 8
+// (512).  At d = 128 a CU holds one workgroup of 8 waves or two of 4, so both
+// take rounds of 512 queries per CU, but a last round of at most one
+// 4-wave workgroup per CU takes about 0.65 of a round (each wave has a SIMD
+// to itself); the second stream of K per CU costs a full round about 5 %.
+// Measured, 8 against 4 waves: 60 / 108 workgroups 66 / 47 us, 120 / 240
+// 131 / 96, 288 / 564 637 / 537, 294 / 588 1461 / 1204, but 432 / 864 506 /
+// 540, 480 / 948 1159 / 1213 and 768 / 1536 2952 / 3040.  At d = 64 a CU
+// holds two of 8 waves: only a grid that leaves it half empty gains (60 / 108
+// 51 / 35 us, 240 / 480 120 / 124).
+static bool mass_small_groups(int heads, int rows, int d) {
+  const int64_t g8 = (int64_t)heads * ((rows + 511) / 512), g4 = (int64_t)heads * ((rows + 255) / 256);
+  if (d == 64) return g4 <= 256;
+  const int64_t rem = g4 % 512;
+  const double t8 = (double)((g8 + 255) / 256);
+  const double t4 = (double)(g4 / 512) + (rem == 0 ? 0.0 : rem <= 256 ? 0.65 : 1.0);
+  return 1.05 * t4 < t8;
+}
+
 size_t mass_scratch_bytes(int BH, int N, int nB) {
   const int ch = mass_chunk_heads(BH, N, nB);
-  return align_up((size_t)ch * nB * N * sizeof(float2)) + align_up((size_t)ch * N * sizeof(float));
+  return align_up((size_t)ch * nB * N * sizeof(float)) + align_up((size_t)ch * N * sizeof(float));
 }
 
 hipError_t launch_mass(View q, View k, int B, int H, int N, int d, int bs, float scale,
@@ -297,32 +370,37 @@ hipError_t launch_mass(View q, View k, int B, int H, int N, int d, int bs, float
   const int nB = (N + bs - 1) / bs;
   const int BH = B * H;
   const int ch = mass_chunk_heads(BH, N, nB);
-  float2 *rec = static_cast<float2 *>(scratch);
-  float *lse2 = reinterpret_cast<float *>(static_cast<char *>(scratch) +
-                                          align_up((size_t)ch * nB * N * sizeof(float2)));
+  float *rec = static_cast<float *>(scratch);
+  float *total = reinterpret_cast<float *>(static_cast<char *>(scratch) +
+                                           align_up((size_t)ch * nB * N * sizeof(float)));
   const float c2 = scale * 1.4426950408889634f;
-  const int qpw = kMassQueries / bs;
   for (int bh0 = 0; bh0 < BH; bh0 += ch) {
     const int nh = std::min(ch, BH - bh0);
-    const dim3 grid((unsigned)(nh * ((nB + qpw - 1) / qpw)));
     hipError_t e = hipSuccess;
-#define CARNATOR_MASS(DD, BB)                                                                    \
+#define CARNATOR_MASS_W(DD, BB, WW)                                                              \
   do {                                                                                           \
-    using C = MassCfg<DD, BB>;                                                                   \
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&mass_pass_kernel<DD, BB>),           \
+    using C = MassCfg<DD, BB, WW>;                                                               \
+    const dim3 grid((unsigned)(nh * ((nB * BB + C::Q - 1) / C::Q)));                             \
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&mass_pass_kernel<DD, BB, WW>),       \
                             hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);                 \
     if (e != hipSuccess) return e;                                                               \
-    hipLaunchKernelGGL((mass_pass_kernel<DD, BB>), grid, dim3(C::NT), C::LDS, s, q, k, H, N, nB, \
-                       bh0, c2, rec, lse2);                                                      \
+    hipLaunchKernelGGL((mass_pass_kernel<DD, BB, WW>), grid, dim3(C::NT), C::LDS, s, q, k, H, N, \
+                       nB, bh0, c2, rec, total);                                                 \
+  } while (0)
+#define CARNATOR_MASS(DD, BB)                                                                    \
+  do {                                                                                           \
+    if (mass_small_groups(nh, nB * BB, DD)) CARNATOR_MASS_W(DD, BB, 4);                          \
+    else CARNATOR_MASS_W(DD, BB, 8);                                                             \
   } while (0)
     if (d == 128 && bs == 128) CARNATOR_MASS(128, 128);
     else if (d == 128 && bs == 64) CARNATOR_MASS(128, 64);
     else if (d == 64 && bs == 128) CARNATOR_MASS(64, 128);
     else CARNATOR_MASS(64, 64);
 #undef CARNATOR_MASS
+#undef CARNATOR_MASS_W
     const int rows = nh * nB;
     hipLaunchKernelGGL(mass_reduce_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, rec,
-                       lse2, N, nB, bs, rows, mass + (int64_t)bh0 * nB * nB);
+                       total, N, nB, bs, rows, mass + (int64_t)bh0 * nB * nB);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;

@@ -52,3 +52,38 @@ def test_selection_ties_across_words(nb, first, last, keep):
     assert (got.cpu().numpy() == want).all()
     bits = P.select_block_mask(torch.as_tensor(mass, device=DEV), float(tau), bits=True)
     np.testing.assert_array_equal(bits.cpu().numpy().view(np.uint64), oracle.pack_mask(got.cpu().numpy()))
+
+
+# The exact masses around the pass's fixed reference: logits whose later keys
+# exceed the first 32 by more than 2^100 or whose keys all lie far below 0
+# (both make a workgroup start over with the row maxima), beside ordinary
+# ones; grids of 4- and of 8-wave workgroups.  Scores are fp32 sums of D bf16
+# products in 3 to 8 roundings of 2^-24 |x|: with |x| up to 600 log2 units a
+# mass is off by 600 * 8 * 6e-8 = 3e-4 relative at most.
+@pytest.mark.parametrize("kind", ["plain", "rising", "low", "mixed"])
+@pytest.mark.parametrize("n,heads,d,bs", [(31, 1, 128, 64), (321, 2, 64, 64), (700, 2, 128, 128), (4161, 1, 64, 128),
+                                          (1100, 90, 128, 64), (1030, 90, 64, 64),
+                                          (500, 256, 128, 128)])
+def test_exact_mass_reference_and_workgroup_sizes(kind, n, heads, d, bs):
+    print("exact mass", kind, n, heads, d, bs, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(n)
+    q = torch.randn(1, heads, n, d, generator=g, device=DEV)
+    k = torch.randn(1, heads, n, d, generator=g, device=DEV)
+    q[..., 0] = 20.0
+    t = torch.arange(n, device=DEV, dtype=torch.float32)
+    root = d ** 0.5 / 20.0  # k[..., 0] = root * y shifts a logit by y
+    if kind == "rising":
+        k[..., 0] = root * 300.0 * t / n
+    elif kind == "low":
+        k[..., 0] = -root * 250.0
+    elif kind == "mixed":
+        k[..., 0] = root * torch.where(t % 97 == 96, 200.0, -150.0)
+    q, k = q.to(torch.bfloat16), k.to(torch.bfloat16)
+    mass = P.block_mass_exact(q, k, bs).cpu().numpy()
+    nb = -(-n // bs)
+    rows = sorted({(0, h, i) for h in (0, heads - 1) for i in (0, nb // 2, nb - 1)})
+    for (b, h, i) in rows:
+        ref = oracle.exact_block_mass(oracle.to_f64(q[:, h:h + 1]), oracle.to_f64(k[:, h:h + 1]), bs, rows=[(b, 0, i)])
+        want = ref[b, 0, i]
+        assert np.abs(mass[b, h, i] - want).max() <= 3e-4 * want.max(), (h, i)
+    np.testing.assert_allclose(mass.sum(-1), 1.0, atol=1e-6)
