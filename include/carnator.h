@@ -225,15 +225,14 @@ int carnator_compact_block_mask(const uint8_t *mask, const carnator_shape *shape
  *   q_hist, k_hist  bf16 views [B, H, N, d]
  *   mass            fp64 [B, H, nB, nB] out
  *   workspace       carnator_block_mass_exact_workspace_size(shape) bytes,
- *                   256-byte aligned: 4 B per (query, key block) plus 4 B
- *                   per query for each head of a chunk.  Heads are processed
- *                   in chunks whose records fit in 4 GiB (at least one head
- *                   per chunk), so the workspace is at most
- *                   max(4 GiB, one head's records): 0.40 GB at B=1, H=12,
- *                   N=32,760, block 128 (all heads in one chunk), 3.99 GB
- *                   at H=24, N=119,056 (9 heads per chunk, 3 chunks),
- *                   2.1 GB for one head at the largest N (2048 blocks of
- *                   128).  A smaller workspace gives E_WORKSPACE.
+ *                   256-byte aligned: 8 B per (query, key block) plus 4 B
+ *                   per query for as many heads as fit in 4 GiB (at least
+ *                   one), so at most max(4 GiB, one head's): 0.81 GB at
+ *                   B=1, H=12, N=32,760, block 128, 3.55 GB at H=24,
+ *                   N=119,056, 4.3 GB for one head at the largest N (2048
+ *                   blocks of 128).  Heads are processed in chunks whose
+ *                   records (4 B per query and key block) fit in it.
+ *                   A smaller workspace gives E_WORKSPACE.
  * Errors: E_NULL, E_SHAPE, E_UNSUPPORTED, E_ALIGN, E_WORKSPACE, E_HIP.
  *
  * carnator_select_block_mask: the selection of carnator_build_block_mask

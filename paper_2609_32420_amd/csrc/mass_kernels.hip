@@ -325,19 +325,23 @@ __global__ void __launch_bounds__(256) mass_reduce_kernel(const float *__restric
 
 }  // namespace
 
-// The records take 4 bytes per (query, key block) of a head: 34 MB at 32K
-// tokens, 443 MB at 119K.  Heads are processed in chunks whose records fit
-// in kMassScratchCap (at least one head per chunk), so the workspace stays
-// bounded whatever the number of heads.
+// The workspace holds 8 bytes per (query, key block) and 4 per query of a
+// head, for as many heads as fit kMassScratchCap (at least one), so it stays
+// bounded whatever the number of heads.  The pass writes 4-byte records: a
+// chunk takes about twice as many heads (34 MB each at 32K tokens, 443 MB at
+// 119K).
 constexpr size_t kMassScratchCap = (size_t)4 << 30;
 
-static size_t mass_head_bytes(int N, int nB) {
-  return ((size_t)nB + 1) * N * sizeof(float);
+size_t mass_scratch_bytes(int BH, int N, int nB) {
+  const size_t per = (size_t)nB * N * 8 + (size_t)N * 4;
+  const size_t ch = std::max<size_t>(1, std::min<size_t>(kMassScratchCap / per, (size_t)BH));
+  return align_up(ch * nB * N * 8) + align_up(ch * N * 4);
 }
 
+// Heads whose records and totals (each array aligned) fit that workspace.
 static int mass_chunk_heads(int BH, int N, int nB) {
-  const size_t per = mass_head_bytes(N, nB);
-  const size_t fit = kMassScratchCap / per;
+  const size_t per = ((size_t)nB + 1) * N * sizeof(float);
+  const size_t fit = (mass_scratch_bytes(BH, N, nB) - kAlign) / per;
   return (int)std::max<size_t>(1, std::min<size_t>(fit, (size_t)BH));
 }
 
@@ -358,11 +362,6 @@ static bool mass_small_groups(int heads, int rows, int d) {
   const double t8 = (double)((g8 + 255) / 256);
   const double t4 = (double)(g4 / 512) + (rem == 0 ? 0.0 : rem <= 256 ? 0.65 : 1.0);
   return 1.05 * t4 < t8;
-}
-
-size_t mass_scratch_bytes(int BH, int N, int nB) {
-  const int ch = mass_chunk_heads(BH, N, nB);
-  return align_up((size_t)ch * nB * N * sizeof(float)) + align_up((size_t)ch * N * sizeof(float));
 }
 
 hipError_t launch_mass(View q, View k, int B, int H, int N, int d, int bs, float scale,
