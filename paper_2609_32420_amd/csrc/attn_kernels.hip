@@ -34,10 +34,8 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // eight bf16 in pairs
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-
-// s_waitcnt immediate: vmcnt(0) with expcnt and lgkmcnt left at their maxima.
-constexpr int kWaitVm0 = 0x0F70;
 
 // The tile loads are driven by hand: the direct loads, the wait and the
 // barrier are written as inline assembly.  Issued through the compiler
@@ -130,16 +128,20 @@ struct Cfg {
 // meets the other waves (after which K(j) and V(j-2) are no longer read) and
 // issues V(j) and K(j+2) into those slots.
 //
-// A grown running max only records alpha: the output accumulators are
-// rescaled at the start of the next iteration, since the P.V in flight in
-// this one still belongs to the old max.  This keeps the softmax free of
-// branches, so it shares one scheduling region with the MFMAs.
-// At d = 64 the kernel is held to 168 registers (a few spills outside the
-// loop), so three workgroups share a CU (their LDS, 3 x 40 KB, fits): with
-// half the MFMAs per score of d = 128 it is bound by its vector work, which a
-// third wave per SIMD overlaps better (2-3 % on the CogVideoX shape; with the
-// LSE, which took 233 registers while its sums were put off, 2.12 -> 2.00 ms
-// on 48 heads of 17,776 tokens).
+// The softmax has one reference per query, the largest score of its first
+// stage: no score waits for its stage's maximum, there is no rescaling, and
+// P is formed evenly under all of the iteration's MFMAs instead of after the
+// maximum.  P, the row sums and O then range over fp32's (bf16's) exponents
+// at the precision they had; a workgroup that finds a row sum beyond 2^100
+// or a sum or output that is not finite walks its row again under running
+// maxima (walk<true>: a grown maximum only records alpha, and O is rescaled
+// at the start of the next iteration, since the P.V in flight belongs to the
+// old one).  Measured against running maxima throughout: 48 heads x 17,776
+// tokens, d = 64, with the LSE 2027 -> 1851 us; lists at d = 128: 12 heads x
+// 32,760 tokens 1673 -> 1618 us, 24 heads x 119,056 tokens 23.8 -> 22.6 ms.
+// At d = 64 the kernel is held to 168 registers, so three workgroups share a
+// CU (their LDS, 3 x 40 KB, fits): with half the MFMAs per score of d = 128
+// it is bound by its vector work, which a third wave per SIMD overlaps better.
 template <int D, int BS, bool WITH_LSE>
 __global__ void __launch_bounds__(2 * BS, D == 64 ? 3 : 2)
 bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, int64_t osh,
@@ -178,8 +180,6 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
       qreg[t] = __builtin_bit_cast(bf16x8, w);
     }
   }
-  // the Q fragment is in registers before any tile load is issued
-  __builtin_amdgcn_s_waitcnt(kWaitVm0);
 
   f32x16 oacc[D / 32];
 #pragma unroll
@@ -244,16 +244,19 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
   // Stage of keys [k0, k0 + KT) reaching past N: its tile starts at
   // k0t = min(k0, N - KT); keys of the tile before k0 (they belong to the
   // previous stage) or at N and beyond are masked.
-  auto mask_tail = [&](f32x16 (&sacc)[MT], int k0) __attribute__((always_inline)) {
+  const int h8 = 8 * hh;
+  auto mask_tile = [&](f32x16 (&sacc)[MT], int mt, int k0) __attribute__((always_inline)) {
     const int k0t = min(k0, kmax);
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int r = 0; r < 16; ++r) {
+      // key k0t + off + 8 hh; the bounds are scalar, so no lane keeps a key
+      const int off = 32 * mt + 16 * (r >> 3) + 4 * ((r >> 2) & 1) + (r & 3);
+      if (h8 < k0 - k0t - off || h8 >= N - k0t - off) sacc[mt][r] = -INFINITY;
+    }
+  };
+  auto mask_tail = [&](f32x16 (&sacc)[MT], int k0) __attribute__((always_inline)) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int g = r >> 2, i = r & 3;
-        const int key = k0t + 32 * mt + 16 * (g >> 1) + 8 * hh + 4 * (g & 1) + i;
-        if (key < k0 || key >= N) sacc[mt][r] = -INFINITY;
-      }
+    for (int mt = 0; mt < MT; ++mt) mask_tile(sacc, mt, k0);
   };
   auto rescale_o = [&]() __attribute__((always_inline)) {
     if (__ballot(alpha != 1.f)) {
@@ -299,13 +302,12 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
     anchor(a);
   };
   // P for scores x, x + 1
-  auto sm_exp = [&](Soft &st, const f32x16 (&sc)[MT], bf16x8 (&pc)[KT / 16], int x) __attribute__((always_inline)) {
+  auto sm_exp = [&](Soft &st, const f32x16 (&sc)[MT], u32x4 (&pc)[KT / 16], int x) __attribute__((always_inline)) {
     const float v0 = __builtin_amdgcn_exp2f(fmaf(sc[x >> 4][x & 15], c2, -st.msub));
     const float v1 = __builtin_amdgcn_exp2f(fmaf(sc[(x + 1) >> 4][(x + 1) & 15], c2, -st.msub));
     const bf16x2 pp = {(__bf16)v0, (__bf16)v1};
     anchor(__builtin_bit_cast(float, pp));
-    pc[x >> 3][x & 7] = pp[0];
-    pc[x >> 3][(x & 7) + 1] = pp[1];
+    pc[x >> 3][(x & 7) >> 1] = __builtin_bit_cast(uint32_t, pp);
     if (((x >> 1) & 1) == 0) st.ps0 = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, st.ps0, false);
     else st.ps1 = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, st.ps1, false);
     if constexpr (WITH_LSE) {
@@ -319,6 +321,7 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
     lrun += st.ps0 + st.ps1;
     if constexpr (WITH_LSE) lexact += st.es0 + st.es1;
     anchor(lrun);
+    st.ps0 = st.ps1 = st.es0 = st.es1 = 0.f;
   };
 
   constexpr int PF = 4;  // operand reads run this many MFMA slots ahead
@@ -339,16 +342,31 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
   // HAS_PV false for j = 0).  The direct loads of V(j) (tile vtp into LDS
   // vdst) and of K(j+2) (ktp, kdst) go one per MFMA slot at the start of
   // part A: issued in one burst they stall the wave behind the vector memory
-  // queue, and issued late they are not there at the next iteration.
-  auto iterate = [&](auto has_pv, auto vs_c, auto ks_c, f32x16 (&sc)[MT], const bf16x8 (&pprev)[KT / 16],
-                     bf16x8 (&pcur)[KT / 16], const uint16_t *vtp, unsigned vdst, const uint16_t *ktp,
-                     unsigned kdst) __attribute__((always_inline)) {
+  // queue, and issued late they are not there at the next iteration.  k0 is
+  // the first key of stage j+1 and tail says that it reaches past N.
+  //
+  // TRACK: the running maximum.  Otherwise every score of a query is taken
+  // against the one reference in mrun, no score waits for its stage's
+  // maximum, and P is formed evenly over the slots: XE pairs of scores of
+  // the stage's first tile as soon as that tile is there, under the second
+  // QK tile of the iteration before (into pprev, whose P is spent by then),
+  // XF pairs in part A, the others under this iteration's first QK tile.
+  constexpr int NPV = (KT / 16) * (D / 32);  // PV MFMAs
+  constexpr int NQK = MT * (D / 16);         // QK MFMAs
+  constexpr int SB = NQK / MT;               // slots before the last QK tile (all of them with one)
+  constexpr int NX = SC / 2;                 // pairs of scores per stage
+  constexpr int XE = MT == 1 ? 0 : D == 128 ? 3 : 2;
+  constexpr int XF = MT == 1 ? NX : 9;
+  static_assert(MT == 1 || (MT == 2 && XE + XF >= 8 && XE <= 8), "the first tile's P is formed in part A at the latest");
+  static_assert(NPV >= 2 * C::LI, "load slots");
+  auto iterate = [&](auto track, auto has_pv, auto vs_c, auto ks_c, Soft &st, f32x16 (&sc)[MT],
+                     u32x4 (&pprev)[KT / 16], u32x4 (&pcur)[KT / 16], const uint16_t *vtp,
+                     unsigned vdst, const uint16_t *ktp, unsigned kdst, bool tail,
+                     int k0) __attribute__((always_inline)) {
+    constexpr bool TRACK = decltype(track)::value;
     constexpr bool HP = decltype(has_pv)::value;
     constexpr int VS = decltype(vs_c)::value, KS = decltype(ks_c)::value;
-    constexpr int NPV = (KT / 16) * (D / 32);  // PV MFMAs
-    constexpr int NQK = MT * (D / 16);         // QK MFMAs
-    static_assert(NPV >= 2 * C::LI, "load slots");
-    Soft st{-INFINITY, -INFINITY, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if constexpr (TRACK) st.m0 = st.m1 = -INFINITY;
     // part A: PV(j-1) | max, alpha, P for the first half of the scores
     {
       bf16x8 vf[NPV];
@@ -359,10 +377,13 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
         const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(lds + base + 4 * C::RB));
         vf[i] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
       };
-      // chunk plan over NPV slots: SC/4 max chunks, the alpha chunk and the
-      // exp pairs of part A (all of them when a stage is one 32-key tile,
-      // whose scores part B overwrites at once; else the first half)
-      constexpr int NCA = SC / 4 + 1 + XA / 2 + (MT == 1 ? 1 : 0);
+      // chunk plan over NPV slots.  TRACK: SC/4 max chunks, the alpha chunk
+      // and the exp pairs of part A (all of them when a stage is one 32-key
+      // tile, whose scores part B overwrites at once; else the first half)
+      constexpr int NM = TRACK ? SC / 4 + 1 : 0;
+      constexpr int NE = TRACK ? XA / 2 : XF;
+      constexpr int X0 = TRACK ? 0 : XE;
+      constexpr int NCA = NM + NE + (MT == 1 ? 1 : 0);
       if constexpr (HP) {
 #pragma unroll
         for (int i = 0; i < PF; ++i) vrd(i);
@@ -372,22 +393,22 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
         if constexpr (HP) {
           if (sl + PF < NPV) vrd(sl + PF);
           const int tp = sl / (D / 32), mo = sl % (D / 32);
-          oacc[mo] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[sl], pprev[tp], oacc[mo], 0, 0, 0);
+          oacc[mo] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[sl], __builtin_bit_cast(bf16x8, pprev[tp]), oacc[mo], 0, 0, 0);
         }
         if (sl < C::LI) dma16(vtp, voff[sl], vdst + sl * 1024);
         else if (sl < 2 * C::LI) dma16(ktp, koff[sl - C::LI], kdst + (sl - C::LI) * 1024);
 #pragma unroll
         for (int c = 0; c < NCA; ++c) {
           if (c * NPV / NCA != sl) continue;
-          if (c < SC / 4) sm_max(st, sc, 4 * c);
-          else if (c == SC / 4) sm_alpha(st);
-          else if (c < SC / 4 + 1 + XA / 2) sm_exp(st, sc, pcur, 2 * (c - SC / 4 - 1));
+          if (c < NM - 1) sm_max(st, sc, 4 * c);
+          else if (c < NM) sm_alpha(st);
+          else if (c < NM + NE) sm_exp(st, sc, pcur, 2 * (X0 + c - NM));
           else sm_done(st);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    // part B: S(j+1) | P for the second half
+    // part B: S(j+1) | P for the other scores
     {
       bf16x8 kf[NQK];
       auto krd = [&](int i) __attribute__((always_inline)) {
@@ -396,8 +417,10 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
       };
 #pragma unroll
       for (int i = 0; i < PF; ++i) krd(i);
-      // the second half of the scores is consumed during the first QK tile
-      constexpr int NCB = MT == 1 ? 0 : (SC - XA) / 2 + 1;
+      // the rest of the scores is consumed during the first QK tile
+      constexpr int XB = TRACK ? XA / 2 : XE + XF;  // pairs done by now
+      constexpr int NCB = MT == 1 ? 0 : NX - XB + 1;
+      constexpr int NCE = TRACK ? 0 : XE;
 #pragma unroll
       for (int sl = 0; sl < NQK; ++sl) {
         if (sl + PF < NQK) krd(sl + PF);
@@ -405,21 +428,32 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
         const int mt = sl / (D / 16), t = sl % (D / 16);
         if (t == 0) sc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[sl], qreg[t], f32x16{}, 0, 0, 0);
         else sc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[sl], qreg[t], sc[mt], 0, 0, 0);
-        constexpr int SB = (MT == 1 ? NQK : NQK / MT);  // slots before the last tile
 #pragma unroll
         for (int c = 0; c < NCB; ++c) {
           if (c * SB / NCB != sl) continue;
-          if (c < (SC - XA) / 2) sm_exp(st, sc, pcur, XA + 2 * c);
+          if (c < NX - XB) sm_exp(st, sc, pcur, 2 * (XB + c));
           else sm_done(st);
+        }
+        if constexpr (NCE > 0) {
+          if (sl == SB && tail) mask_tile(sc, 0, k0);
+#pragma unroll
+          for (int c = 0; c < NCE; ++c)
+            if (SB + 1 + c * (SB - 1) / NCE == sl) sm_exp(st, sc, pprev, 2 * c);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
+    if (tail) {
+      if constexpr (!TRACK && MT == 2) mask_tile(sc, 1, k0);
+      else mask_tail(sc, k0);
+    }
   };
 
-  if (e1 > e0) {
+  // The row's key blocks in turn: O, the row sums and mrun.
+  auto walk = [&](auto track) __attribute__((always_inline)) {
+    constexpr bool TRACK = decltype(track)::value;
     f32x16 sc[MT];
-    bf16x8 pa[KT / 16], pb[KT / 16];
+    u32x4 pa[KT / 16], pb[KT / 16];
     using T = std::true_type;
     using F = std::false_type;
     using I0 = std::integral_constant<int, 0>;
@@ -436,9 +470,21 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
       issue_tile(tile_base(kbase, k.sn, min(k0 + KT, kmax)), koff, wdst + C::TB);
     }
     for (int i = threadIdx.x; i < L; i += C::NT) list[i] = min(max(col_idx[e0 + i], 0), nB - 1);
+    if (!TRACK && threadIdx.x == 0) list[kMaxListBlocks] = 0;  // no query left its range yet
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     qk_plain(sc);
     if (blk0 * BS + KT > N) mask_tail(sc, blk0 * BS);
+    Soft st{-INFINITY, -INFINITY, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if constexpr (!TRACK) {
+      // the query's reference: the largest score of its first stage
+#pragma unroll
+      for (int x = 0; x < SC; x += 4) sm_max(st, sc, x);
+      const float2 hv = halves(__builtin_fmaxf(st.m0, st.m1));
+      const float m = __builtin_fmaxf(hv.x, hv.y) * c2;
+      mrun = st.msub = m == -INFINITY ? 0.f : m;
+#pragma unroll
+      for (int c = 0; c < XE; ++c) sm_exp(st, sc, pa, 2 * c);
+    }
 
     // Stages come in pairs (both halves of block b): iteration 2b loads V(2b)
     // (first half of block b) and K(2b+2) (first half of block b+1),
@@ -449,24 +495,23 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
       const bool more = b + 1 < L;
       // even stage j = 2b
       wait_all_then_barrier();
-      if constexpr (!decltype(first)::value) rescale_o();
+      if constexpr (TRACK && !decltype(first)::value) rescale_o();
       {
         const int kv = blk0 * BS;
         const int kk = more ? blk1 * BS : 0;
-        iterate(std::integral_constant<bool, !decltype(first)::value>{}, I1{}, I1{}, sc, pb, pa,
+        iterate(track, std::integral_constant<bool, !decltype(first)::value>{}, I1{}, I1{}, st, sc, pb, pa,
                 tile_base(vbase, v.sn, min(kv, kmax)), wdst + 2 * C::TB,
-                tile_base(kbase, k.sn, min(kk, kmax)), wdst);
-        if (blk0 * BS + 2 * KT > N) mask_tail(sc, blk0 * BS + KT);  // S(2b+1)
+                tile_base(kbase, k.sn, min(kk, kmax)), wdst, blk0 * BS + 2 * KT > N, blk0 * BS + KT);  // S(2b+1)
       }
       // odd stage j = 2b+1
       wait_all_then_barrier();
-      rescale_o();
+      if constexpr (TRACK) rescale_o();
       {
         const int kv = blk0 * BS + KT;
         const int kk = more ? blk1 * BS + KT : 0;
-        iterate(T{}, I0{}, I0{}, sc, pa, pb, tile_base(vbase, v.sn, min(kv, kmax)), wdst + 3 * C::TB,
-                tile_base(kbase, k.sn, min(kk, kmax)), wdst + C::TB);
-        if (more && blk1 * BS + KT > N) mask_tail(sc, blk1 * BS);  // S(2b+2)
+        iterate(track, T{}, I0{}, I0{}, st, sc, pa, pb, tile_base(vbase, v.sn, min(kv, kmax)), wdst + 3 * C::TB,
+                tile_base(kbase, k.sn, min(kk, kmax)), wdst + C::TB, more && blk1 * BS + KT > N,
+                blk1 * BS);  // S(2b+2)
       }
       blk0 = blk1;
       blk1 = __builtin_amdgcn_readfirstlane(nxt);
@@ -475,8 +520,8 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
     for (int b = 1; b < L; ++b) pair(F{}, b);
     // P.V of the last stage (odd: V slot 1, P in pb)
     wait_all_then_barrier();
-    rescale_o();
-    auto pv_last = [&](auto vs_c, const bf16x8 (&pl)[KT / 16]) __attribute__((always_inline)) {
+    if constexpr (TRACK) rescale_o();
+    auto pv_last = [&](auto vs_c, const u32x4 (&pl)[KT / 16]) __attribute__((always_inline)) {
 #pragma unroll
       for (int tp = 0; tp < KT / 16; ++tp)
 #pragma unroll
@@ -485,10 +530,39 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
           const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(lds + base));
           const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(lds + base + 4 * C::RB));
           const bf16x8 av = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-          oacc[mo] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, pl[tp], oacc[mo], 0, 0, 0);
+          oacc[mo] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, __builtin_bit_cast(bf16x8, pl[tp]), oacc[mo], 0, 0, 0);
         }
     };
     pv_last(I1{}, pb);
+  };
+
+  if (e1 > e0) {
+    walk(std::false_type{});
+    // A query whose scores outgrew its reference (row sum or output not
+    // finite, or the sum beyond 2^100), or whose inputs are not finite: the
+    // workgroup walks the row again under running maxima.
+    float t0 = 0.f, t1 = 0.f;
+#pragma unroll
+    for (int mo = 0; mo < D / 32; ++mo)
+#pragma unroll
+      for (int r = 0; r < 16; r += 2) {
+        t0 = fmaf(oacc[mo][r], 0.f, t0);
+        t1 = fmaf(oacc[mo][r + 1], 0.f, t1);
+      }
+    const bool fine = lrun <= 0x1p100f && t0 + t1 == 0.f;
+    volatile int *flag = reinterpret_cast<int *>(lds + C::LIST) + kMaxListBlocks;
+    if (__ballot(!fine) != 0 && lane == 0) *flag = 1;
+    wait_all_then_barrier();
+    if (__builtin_amdgcn_readfirstlane(*flag) != 0) {
+#pragma unroll
+      for (int mo = 0; mo < D / 32; ++mo)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[mo][r] = 0.f;
+      mrun = -INFINITY;
+      lrun = lexact = 0.f;
+      alpha = 1.f;
+      walk(std::true_type{});
+    }
   }
 
   // ---- epilogue: normalise, store bf16 O (and the LSE)

@@ -87,3 +87,66 @@ def test_exact_mass_reference_and_workgroup_sizes(kind, n, heads, d, bs):
         want = ref[b, 0, i]
         assert np.abs(mass[b, h, i] - want).max() <= 3e-4 * want.max(), (h, i)
     np.testing.assert_allclose(mass.sum(-1), 1.0, atol=1e-6)
+
+
+# Attention around the one reference per query (the largest score of the first
+# half block): logits whose later keys exceed it by 2^60 (in range), by more
+# than 2^100 or 2^128 (the workgroup walks the row again under running
+# maxima), all far below 0, or mixed between the workgroup's queries; values
+# near the largest bf16, whose products overflow beside a grown reference.
+# Logits here reach 600 in log2 units and carry up to D / 16 + 1 fp32
+# roundings of 2^-24 of that each: 3e-4 relative on a probability, far below
+# the bf16 rounding of P and O (2^-8 each) that the tolerances are for.
+@pytest.mark.parametrize("kind", ["plain", "rise60", "rise120", "rise300", "low", "mixed", "huge"])
+@pytest.mark.parametrize("n,d,bs", [(1000, 128, 128), (1000, 64, 128), (690, 128, 64), (690, 64, 64), (40, 64, 128)])
+def test_attention_reference_range(kind, n, d, bs):
+    print("attention reference", kind, n, d, bs, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(n + d)
+    q, k, v = (torch.randn(1, 2, n, d, generator=g, device=DEV) for _ in range(3))
+    t = torch.arange(n, device=DEV, dtype=torch.float32)
+    q[..., 0] = 20.0
+    unit = d ** 0.5 / 20.0 * 0.6931  # k[..., 0] = unit * y shifts a logit by y in log2 units
+    if kind.startswith("rise"):
+        k[..., 0] = unit * float(kind[4:]) * t / n
+    elif kind == "low":
+        k[..., 0] = -unit * 250.0
+    elif kind == "mixed":
+        k[..., 0] = unit * torch.where(t % 97 == 96, 200.0, -150.0)
+        q[..., 0] = torch.where(t % 3 == 0, 20.0, 1.0)
+    elif kind == "huge":
+        k[..., 0] = unit * 90.0 * t / n
+        v *= 2.0 ** 100
+    q, k, v = (x.to(torch.bfloat16) for x in (q, k, v))
+    nb = -(-n // bs)
+    m = (np.random.default_rng(n).random((1, 2, nb, nb)) < 0.5).astype(np.uint8)
+    m[..., -1] |= m.sum(-1) == 0
+    m[0, 0, :, -1] = 1  # the partial block in every list of one head
+    dm = torch.as_tensor(m, device=DEV)
+    o, lse = P.block_sparse_attn(q, k, v, dm, bs, return_lse=True)
+    assert torch.equal(o, P.block_sparse_attn(q, k, v, dm, bs))
+    ro, rl = oracle.block_sparse_attention(oracle.to_f64(q), oracle.to_f64(k), oracle.to_f64(v), m, bs)
+    got = o.double().cpu().numpy()
+    unit_v = 2.0 ** 100 if kind == "huge" else 1.0
+    assert np.abs(got - ro).max() <= 2e-2 * unit_v * max(1.0, np.abs(ro).max() / unit_v / 2)
+    assert np.linalg.norm(got - ro) <= 5e-3 * np.linalg.norm(ro)
+    assert np.abs(lse.double().cpu().numpy() - rl).max() <= 1e-3
+
+
+# Inputs that are not finite give what they gave under running maxima: an
+# infinite value reaches exactly the queries whose lists hold it.
+def test_attention_infinite_values():
+    n, d, bs = 600, 128, 128
+    g = torch.Generator(device=DEV).manual_seed(5)
+    q, k, v = (torch.randn(1, 1, n, d, generator=g, device=DEV).to(torch.bfloat16) for _ in range(3))
+    v[0, 0, 200, 7] = float("inf")  # key block 1
+    m = np.ones((1, 1, 5, 5), np.uint8)
+    m[0, 0, ::2, 1] = 0
+    o = P.block_sparse_attn(q, k, v, torch.as_tensor(m, device=DEV), bs)
+    seen = torch.isinf(o[0, 0, :, 7])
+    holds = torch.arange(n, device=DEV) // bs % 2 == 1
+    assert torch.equal(seen, holds)
+    assert torch.isfinite(o[0, 0][:, torch.arange(d, device=DEV) != 7]).all()
+    clean = v.clone()
+    clean[0, 0, 200, 7] = 0
+    want = P.block_sparse_attn(q, k, clean, torch.as_tensor(m, device=DEV), bs)
+    assert torch.equal(o[0, 0, ~holds], want[0, 0, ~holds])
