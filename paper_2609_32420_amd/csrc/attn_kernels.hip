@@ -129,13 +129,15 @@ struct Cfg {
 // issues V(j) and K(j+2) into those slots.
 //
 // The softmax has one reference per query, the largest score of its first
-// stage: no score waits for its stage's maximum, there is no rescaling, and
-// P is formed evenly under all of the iteration's MFMAs instead of after the
-// maximum.  P, the row sums and O then range over fp32's (bf16's) exponents
-// at the precision they had; a workgroup that finds a row sum beyond 2^100
-// or a sum or output that is not finite walks its row again under running
-// maxima (walk<true>: a grown maximum only records alpha, and O is rescaled
-// at the start of the next iteration, since the P.V in flight belongs to the
+// stage or 0 if that is less: no score waits for its stage's maximum, there
+// is no rescaling, and P is formed evenly under all of the iteration's MFMAs
+// instead of after the maximum.  P, the row sums and O then range over
+// fp32's (bf16's) exponents at the precision they had, and with a reference
+// of at least 0 the fma rounds x - r no coarser than x itself where x carries
+// weight.  A workgroup that finds a row sum outside [2^-40, 2^100] or an
+// output that is not finite walks its row again under running maxima
+// (walk<true>: a grown maximum only records alpha, and O is rescaled at the
+// start of the next iteration, since the P.V in flight belongs to the
 // old one).  Measured against running maxima throughout: 48 heads x 17,776
 // tokens, d = 64, with the LSE 2027 -> 1851 us; lists at d = 128: 12 heads x
 // 32,760 tokens 1673 -> 1618 us, 24 heads x 119,056 tokens 23.8 -> 22.6 ms.
@@ -476,12 +478,13 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
     if (blk0 * BS + KT > N) mask_tail(sc, blk0 * BS);
     Soft st{-INFINITY, -INFINITY, 0.f, 0.f, 0.f, 0.f, 0.f};
     if constexpr (!TRACK) {
-      // the query's reference: the largest score of its first stage
+      // the query's reference: the largest score of its first stage, at
+      // least 0
 #pragma unroll
       for (int x = 0; x < SC; x += 4) sm_max(st, sc, x);
       const float2 hv = halves(__builtin_fmaxf(st.m0, st.m1));
       const float m = __builtin_fmaxf(hv.x, hv.y) * c2;
-      mrun = st.msub = m == -INFINITY ? 0.f : m;
+      mrun = st.msub = __builtin_fmaxf(m, 0.f);
 #pragma unroll
       for (int c = 0; c < XE; ++c) sm_exp(st, sc, pa, 2 * c);
     }
@@ -538,9 +541,9 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
 
   if (e1 > e0) {
     walk(std::false_type{});
-    // A query whose scores outgrew its reference (row sum or output not
-    // finite, or the sum beyond 2^100), or whose inputs are not finite: the
-    // workgroup walks the row again under running maxima.
+    // A query whose scores lie far from its reference (a row sum outside
+    // [2^-40, 2^100], or an output that is not finite), or whose inputs are
+    // not finite: the workgroup walks the row again under running maxima.
     float t0 = 0.f, t1 = 0.f;
 #pragma unroll
     for (int mo = 0; mo < D / 32; ++mo)
@@ -549,7 +552,9 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
         t0 = fmaf(oacc[mo][r], 0.f, t0);
         t1 = fmaf(oacc[mo][r + 1], 0.f, t1);
       }
-    const bool fine = lrun <= 0x1p100f && t0 + t1 == 0.f;
+    const float2 lw = halves(lrun);
+    const float lsum = lw.x + lw.y;
+    const bool fine = lsum >= 0x1p-40f && lsum <= 0x1p100f && t0 + t1 == 0.f;
     volatile int *flag = reinterpret_cast<int *>(lds + C::LIST) + kMaxListBlocks;
     if (__ballot(!fine) != 0 && lane == 0) *flag = 1;
     wait_all_then_barrier();

@@ -90,15 +90,16 @@ def test_exact_mass_reference_and_workgroup_sizes(kind, n, heads, d, bs):
 
 
 # Attention around the one reference per query (the largest score of the first
-# half block): logits whose later keys exceed it by 2^60 (in range), by more
+# 64 keys, at least 0): logits whose later keys exceed it by 2^60 (in range), by more
 # than 2^100 or 2^128 (the workgroup walks the row again under running
-# maxima), all far below 0, or mixed between the workgroup's queries; values
+# maxima), all 30 below 0 (in range) or 250 (walked again), or mixed between the workgroup's queries; values
 # near the largest bf16, whose products overflow beside a grown reference.
 # Logits here reach 600 in log2 units and carry up to D / 16 + 1 fp32
 # roundings of 2^-24 of that each: 3e-4 relative on a probability, far below
 # the bf16 rounding of P and O (2^-8 each) that the tolerances are for.
-@pytest.mark.parametrize("kind", ["plain", "rise60", "rise120", "rise300", "low", "mixed", "huge"])
-@pytest.mark.parametrize("n,d,bs", [(1000, 128, 128), (1000, 64, 128), (690, 128, 64), (690, 64, 64), (40, 64, 128)])
+@pytest.mark.parametrize("kind", ["plain", "rise60", "rise120", "rise300", "low", "low30", "mixed", "huge"])
+@pytest.mark.parametrize("n,d,bs", [(1000, 128, 128), (1000, 64, 128), (690, 128, 64), (690, 64, 64), (40, 64, 128),
+                                    (50, 64, 64), (70, 64, 64), (150, 64, 64)])
 def test_attention_reference_range(kind, n, d, bs):
     print("attention reference", kind, n, d, bs, flush=True)
     g = torch.Generator(device=DEV).manual_seed(n + d)
@@ -108,8 +109,8 @@ def test_attention_reference_range(kind, n, d, bs):
     unit = d ** 0.5 / 20.0 * 0.6931  # k[..., 0] = unit * y shifts a logit by y in log2 units
     if kind.startswith("rise"):
         k[..., 0] = unit * float(kind[4:]) * t / n
-    elif kind == "low":
-        k[..., 0] = -unit * 250.0
+    elif kind.startswith("low"):
+        k[..., 0] = -unit * float(kind[3:] or 250)
     elif kind == "mixed":
         k[..., 0] = unit * torch.where(t % 97 == 96, 200.0, -150.0)
         q[..., 0] = torch.where(t % 3 == 0, 20.0, 1.0)
