@@ -3,13 +3,13 @@
 // recomputed and only the key blocks listed for a query block are visited.
 //
 // One workgroup per query block (BS queries, BS/32 waves of 32 queries).  The
-// workgroup walks its compacted key-block list in stages of BS/2 keys (half a
-// key block).  K and V stages are copied from HBM straight into LDS
+// workgroup walks its compacted key-block list in stages of KT keys (a key
+// block or half of one).  K and V stages are copied from HBM straight into LDS
 // (global_load_lds, no register staging) into two slots each: the K tile of a
 // stage is issued two stages before its scores are computed, the V tile one
 // stage before its P.V product.  S^T = K Q^T and O^T += V^T P^T run on bf16
-// MFMA 32x32x16 with fp32 accumulation; the online softmax runs in fp32 in
-// the exp2 domain.
+// MFMA 32x32x16 with fp32 accumulation; the softmax runs in fp32 in the
+// exp2 domain.
 //
 // Computing S^T (keys as MFMA rows, queries as columns) puts every score of a
 // query in one lane pair (lane q and lane q+32), so the row max is one
@@ -98,7 +98,14 @@ constexpr int kMaxListBlocks = 2048;
 
 template <int D, int BS>
 struct Cfg {
-  static constexpr int KT = BS / 2;               // keys per stage (two stages per block)
+  // Keys per stage: half a key block, but a whole one at d = 64 with 64-token
+  // blocks: 32 keys there are 8 MFMAs a wave, too few to load the next tiles
+  // under (48 heads x 17,776 tokens 2438 -> 2360 us, 6 x 4000 41.1 -> 37.0).
+  // At d = 128 its 74 KB of LDS leave two workgroups per CU instead of three,
+  // which costs more wherever there are more than two to run (24 x 8000
+  // tokens 565 -> 595 us, 12 x 4000 116 -> 142; 2 x 6 x 1988 42.7 -> 38.5).
+  static constexpr int KT = BS == 128 || D == 64 ? 64 : 32;
+  static constexpr int SPB = BS / KT;             // stages per key block
   static constexpr int MT = KT / 32;              // 32-key MFMA tiles per stage
   static constexpr int WAVES = BS / 32;
   static constexpr int NT = 64 * WAVES;
@@ -145,7 +152,7 @@ struct Cfg {
 // CU (their LDS, 3 x 40 KB, fits): with half the MFMAs per score of d = 128
 // it is bound by its vector work, which a third wave per SIMD overlaps better.
 template <int D, int BS, bool WITH_LSE>
-__global__ void __launch_bounds__(2 * BS, D == 64 ? 3 : 2)
+__global__ void __launch_bounds__(2 * BS, D == 64 && BS == 128 ? 3 : 2)
 bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, int64_t osh,
               int64_t osn, int H, int N, int nB, const int32_t *__restrict__ row_ptr,
               const int32_t *__restrict__ col_idx, const int32_t *__restrict__ order,
@@ -460,16 +467,16 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
     using F = std::false_type;
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
-    const int L = e1 - e0;  // key blocks of the row; stages 2b and 2b+1 are block b
+    const int L = e1 - e0;  // key blocks of the row; with SPB = 2 stages 2b and 2b+1 are block b
     int *list = reinterpret_cast<int *>(lds + C::LIST);
-    // prologue: K(0), K(1) (both halves of block 0), the row's list into LDS;
-    // S(0)
+    // prologue: K(0), K(1) (both halves of block 0, or blocks 0 and 1), the
+    // row's list into LDS; S(0)
     int blk0 = min(max(col_idx[e0], 0), nB - 1);
     int blk1 = L > 1 ? min(max(col_idx[e0 + 1], 0), nB - 1) : 0;
     {
-      const int k0 = blk0 * BS;
+      const int k0 = blk0 * BS, k1 = C::SPB == 2 ? k0 + KT : blk1 * BS;
       issue_tile(tile_base(kbase, k.sn, min(k0, kmax)), koff, wdst);
-      issue_tile(tile_base(kbase, k.sn, min(k0 + KT, kmax)), koff, wdst + C::TB);
+      issue_tile(tile_base(kbase, k.sn, min(k1, kmax)), koff, wdst + C::TB);
     }
     for (int i = threadIdx.x; i < L; i += C::NT) list[i] = min(max(col_idx[e0 + i], 0), nB - 1);
     if (!TRACK && threadIdx.x == 0) list[kMaxListBlocks] = 0;  // no query left its range yet
@@ -519,9 +526,36 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
       blk0 = blk1;
       blk1 = __builtin_amdgcn_readfirstlane(nxt);
     };
-    pair(T{}, 0);
-    for (int b = 1; b < L; ++b) pair(F{}, b);
-    // P.V of the last stage (odd: V slot 1, P in pb)
+    if constexpr (C::SPB == 2) {
+      pair(T{}, 0);
+      for (int b = 1; b < L; ++b) pair(F{}, b);
+    } else {
+      // A block per stage: iteration j loads V(j) and K(j+2), blocks j .. j+2
+      // in blk0 .. blk2 (past the list's end its last block again, unused).
+      int blk2 = __builtin_amdgcn_readfirstlane(list[min(2, L - 1)]);
+      auto stage = [&](auto first, auto odd, int j) __attribute__((always_inline)) {
+        constexpr bool O = decltype(odd)::value;
+        using Slot = std::integral_constant<int, O ? 0 : 1>;  // of V(j-1) and K(j+1)
+        const int nxt = list[min(j + 3, L - 1)];
+        wait_all_then_barrier();
+        if constexpr (TRACK && !decltype(first)::value) rescale_o();
+        const unsigned to = wdst + (O ? C::TB : 0);
+        iterate(track, std::integral_constant<bool, !decltype(first)::value>{}, Slot{}, Slot{}, st, sc, O ? pa : pb,
+                O ? pb : pa, tile_base(vbase, v.sn, min(blk0 * BS, kmax)), to + 2 * C::TB,
+                tile_base(kbase, k.sn, min(blk2 * BS, kmax)), to, j + 1 < L && blk1 * BS + KT > N, blk1 * BS);
+        blk0 = blk1;
+        blk1 = blk2;
+        blk2 = __builtin_amdgcn_readfirstlane(nxt);
+      };
+      stage(T{}, F{}, 0);
+      int j = 1;
+      for (; j + 1 < L; j += 2) {
+        stage(F{}, T{}, j);
+        stage(F{}, F{}, j + 1);
+      }
+      if (j < L) stage(F{}, T{}, j);
+    }
+    // P.V of the last stage (odd: V slot 1, P in pb; even: V slot 0, P in pa)
     wait_all_then_barrier();
     if constexpr (TRACK) rescale_o();
     auto pv_last = [&](auto vs_c, const u32x4 (&pl)[KT / 16]) __attribute__((always_inline)) {
@@ -536,7 +570,8 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
           oacc[mo] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, __builtin_bit_cast(bf16x8, pl[tp]), oacc[mo], 0, 0, 0);
         }
     };
-    pv_last(I1{}, pb);
+    if (C::SPB == 2 || (L & 1) == 0) pv_last(I1{}, pb);
+    else pv_last(I0{}, pa);
   };
 
   if (e1 > e0) {
