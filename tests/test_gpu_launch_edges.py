@@ -151,3 +151,39 @@ def test_attention_infinite_values():
     clean[0, 0, 200, 7] = 0
     want = P.block_sparse_attn(q, k, clean, torch.as_tensor(m, device=DEV), bs)
     assert torch.equal(o[0, 0, ~holds], want[0, 0, ~holds])
+
+
+# Compaction of few rows in one launch: up to 128 words of 64 key blocks from
+# bytes and 256 from bits, and one more of either; one and several words per
+# row, empty and full rows.
+@pytest.mark.parametrize("batch,heads,nb", [(1, 1, 1), (1, 1, 2), (2, 3, 3), (1, 128, 1), (1, 129, 1), (1, 256, 1),
+                                            (1, 257, 1), (1, 2, 64), (2, 2, 64), (1, 5, 64), (1, 1, 65), (1, 2, 65),
+                                            (1, 1, 128), (1, 1, 129), (2, 6, 16), (1, 8, 16)])
+@pytest.mark.parametrize("density", [0.0, 0.3, 1.0])
+def test_compaction_of_few_rows(batch, heads, nb, density):
+    rng = np.random.default_rng(1000 * nb + heads)
+    m = (rng.random((batch, heads, nb, nb)) < density).astype(np.uint8) * np.uint8(3)
+    m[0, 0, nb // 2] = 0
+    m[-1, -1, -1] = 1
+    one = (m != 0).astype(np.uint8)
+
+    def same(got, want):
+        for a, b in zip(got, want):
+            np.testing.assert_array_equal(a.cpu().numpy()[:len(b)], b)
+
+    dm = torch.as_tensor(m, device=DEV)
+    same(P.compact_block_mask(dm), oracle.compact_mask(one))
+    packed = oracle.pack_mask(one)
+    if nb % 64:
+        packed[..., -1] |= np.uint64(1) << np.uint64(63)  # an unused bit: ignored
+    bits = torch.as_tensor(packed.view(np.int64), device=DEV)
+    same(P.compact_block_mask_bits(bits), oracle.compact_mask(one))
+    rows = (rng.random((batch, nb)) < 0.2).astype(np.uint8)
+    cols = (rng.random((batch, nb)) < 0.1).astype(np.uint8)
+    same(P.compact_block_mask_bits(bits, rows, cols), oracle.compact_mask(oracle.merge_target_rows(one, rows, cols)))
+    for act in (rows, np.zeros_like(rows), np.ones_like(rows)):
+        ctx = np.maximum(act, cols)
+        got = P.compact_block_mask_bits_region(bits, act, ctx)
+        want = oracle.compact_restricted(one, act, ctx)
+        same(got[:3], want[:3])
+        assert int(got[3].item()) == want[3]
