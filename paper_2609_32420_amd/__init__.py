@@ -127,12 +127,16 @@ def _check(status: int):
         raise CarnatorError(status, lib().carnator_last_error().decode())
 
 
-def _stream(t: torch.Tensor):
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+def _stream(t: torch.Tensor) -> int:
+    """The current stream of t's device (the raw handle: a Stream object costs
+    a microsecond or two to make, as much as a launch)."""
+    if t.is_cuda:
+        return torch._C._cuda_getCurrentRawStream(t.get_device())
+    return torch.cuda.current_stream(t.device).cuda_stream  # raises
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
 
 
 def _shape(t: torch.Tensor, block: int) -> Shape:
@@ -165,9 +169,12 @@ def order_group_heads(batch: int, heads: int, nb: int, attn=None) -> int:
 
 
 def _view(t: torch.Tensor) -> View:
-    if t.dim() != 4 or t.dtype != torch.bfloat16 or not t.is_cuda or t.stride(3) != 1:
+    if t.dim() != 4 or t.dtype != torch.bfloat16 or not t.is_cuda:
         raise ValueError("expected a bf16 CUDA tensor [B, H, N, d] with d contiguous")
-    return View(t.data_ptr(), t.stride(0), t.stride(1), t.stride(2))
+    sb, sh, sn, sd = t.stride()
+    if sd != 1:
+        raise ValueError("expected a bf16 CUDA tensor [B, H, N, d] with d contiguous")
+    return View(t.data_ptr(), sb, sh, sn)
 
 
 def _workspace(nbytes: int, device) -> torch.Tensor:
@@ -178,11 +185,12 @@ def _workspace(nbytes: int, device) -> torch.Tensor:
 def _dev_u8(x, device, shape) -> Optional[torch.Tensor]:
     if x is None:
         return None
-    x = torch.as_tensor(x, device=device)
+    if not (isinstance(x, torch.Tensor) and x.device == device):
+        x = torch.as_tensor(x, device=device)
     if x.dtype != torch.uint8:
         x = (x != 0).to(torch.uint8)
     x = x.contiguous()
-    if tuple(x.shape) != tuple(shape):
+    if x.shape != shape:
         raise ValueError("flags must have shape %s" % (tuple(shape),))
     return x
 
@@ -201,7 +209,7 @@ def build_block_mask(q_hist: torch.Tensor, k_hist: torch.Tensor, block: int, mas
                      workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Historical block mask uint8 [B, H, nB, nB] (carnator_build_block_mask)."""
     s = _shape(q_hist, block)
-    if tuple(k_hist.shape) != tuple(q_hist.shape):
+    if k_hist.shape != q_hist.shape:
         raise ValueError("q_hist and k_hist shapes differ")
     nb = -(-s.seq_len // block)
     if out is None:
@@ -220,7 +228,7 @@ def block_mass_exact(q_hist: torch.Tensor, k_hist: torch.Tensor, block: int, sca
     """Token-level attention mass of every block pair, fp64 [B, H, nB, nB]
     (carnator_block_mass_exact)."""
     s = _shape(q_hist, block)
-    if tuple(k_hist.shape) != tuple(q_hist.shape):
+    if k_hist.shape != q_hist.shape:
         raise ValueError("q_hist and k_hist shapes differ")
     nb = -(-s.seq_len // block)
     if out is None:
@@ -335,7 +343,7 @@ def build_block_mask_bits(q_hist: torch.Tensor, k_hist: torch.Tensor, block: int
     """Historical block mask, bit-packed: int64 [B, H, nB, W]
     (carnator_build_block_mask_bits)."""
     s = _shape(q_hist, block)
-    if tuple(k_hist.shape) != tuple(q_hist.shape):
+    if k_hist.shape != q_hist.shape:
         raise ValueError("q_hist and k_hist shapes differ")
     nb = -(-s.seq_len // block)
     if out is None:
@@ -462,7 +470,7 @@ def block_sparse_attn(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, mask: t
     (carnator_block_sparse_attn).  Returns O (and the fp32 LSE)."""
     s = _shape(q, block)
     for t, n in ((k, "k"), (v, "v")):
-        if tuple(t.shape) != tuple(q.shape):
+        if t.shape != q.shape:
             raise ValueError("%s shape differs from q" % n)
     nb = -(-s.seq_len // block)
     if tuple(mask.shape) != (s.batch, s.heads, nb, nb) or mask.dtype != torch.uint8 or not mask.is_contiguous():
@@ -491,7 +499,7 @@ def block_sparse_attn_lists(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, l
     rest of ``out`` (and of ``lse``, which may be passed in) is untouched."""
     s = _shape(q, block)
     for t, n in ((k, "k"), (v, "v")):
-        if tuple(t.shape) != tuple(q.shape):
+        if t.shape != q.shape:
             raise ValueError("%s shape differs from q" % n)
     row_ptr, col_idx, order = lists
     nb = -(-s.seq_len // block)
@@ -553,7 +561,7 @@ def latent_fusion(z_target: torch.Tensor, z_hist: torch.Tensor, weight: torch.Te
     for t, n in ((z_target, "z_target"), (z_hist, "z_hist")):
         if t.dim() != 5 or t.dtype != torch.float32 or not t.is_contiguous():
             raise ValueError("%s must be a contiguous fp32 [B, C, T, H, W] tensor" % n)
-    if tuple(z_hist.shape) != tuple(z_target.shape):
+    if z_hist.shape != z_target.shape:
         raise ValueError("z_hist shape differs from z_target")
     if weight.dim() != 4 or weight.dtype != torch.float32 or not weight.is_contiguous():
         raise ValueError("weight must be a contiguous fp32 [B, T, H, W] tensor")
