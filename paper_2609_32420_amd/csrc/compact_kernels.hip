@@ -411,6 +411,68 @@ __global__ void __launch_bounds__(kScanThreads) sort_hist_kernel(const int32_t *
   if (t == 0) csum[c] = total;
 }
 
+// The same from packed rows of at most kCountWords words, with the lengths
+// (written to len) and the packing of the dense-column flags (cols uint8
+// [B][nB] or NULL, to colw) in the same launch: a thread counts its row, the
+// column words of the chunk's batch entries sit in LDS behind the counters.
+// Two launches fewer than packing, counting and this: lists of 12 heads of 256
+// blocks restricted to a region 14.7 -> 12.1 us a call in a stream of them,
+// of 24 heads of 64 blocks 12.7 -> 9.8; without column flags 12.3 -> 11.2 and
+// 10.2 -> 9.1.  Longer rows keep the count over the whole chip: here one CU
+// per chunk reads its rows' words, a row per lane.
+constexpr int kCountWords = 4;
+__global__ void __launch_bounds__(kScanThreads) sort_hist_bits_kernel(
+    const uint64_t *__restrict__ bits, Chunks ch, int nB, int HnB, const uint8_t *__restrict__ rows,
+    const uint8_t *__restrict__ cols, bool narrow, uint64_t *__restrict__ colw, int32_t *__restrict__ len,
+    int32_t *__restrict__ hist, int32_t *__restrict__ csum, int32_t *__restrict__ rloc) {
+  extern __shared__ uint64_t cw[];  // the column words of batch entries b0 ..., then nB + 2 counters
+  __shared__ int sh[kSortWaves];
+  const int c = blockIdx.x, t = threadIdx.x, lane = t & 63;
+  const int K = nB + 2, nw = (nB + 63) / 64;
+  const int lo = (int)ch.lo(c), hi = (int)ch.hi(c);  // a chunk holds at least one row
+  const int b0 = lo / HnB;
+  const int ncw = cols != nullptr ? ((hi - 1) / HnB - b0 + 1) * nw : 0;
+  int *hk = reinterpret_cast<int *>(cw + ncw);
+  const int r = lo + t;
+  const bool on = r < hi;
+  const int rc = on ? r : hi - 1;
+  uint64_t w[kCountWords];
+#pragma unroll
+  for (int u = 0; u < kCountWords; ++u) w[u] = bits[(int64_t)rc * nw + min(u, nw - 1)];
+  const int b = rc / HnB;
+  const bool flag = rows != nullptr && rows[(int64_t)b * nB + rc % nB] != 0;
+  for (int x = __builtin_amdgcn_readfirstlane(t >> 6); x < ncw; x += kSortWaves) {
+    const int bb = x / nw, j = (x - bb * nw) * 64 + lane;
+    const uint64_t word = __ballot(j < nB && cols[(int64_t)(b0 + bb) * nB + min(j, nB - 1)] != 0);
+    if (lane == 0) {
+      cw[x] = word;
+      // each batch entry by the chunk that holds its first row
+      if ((b0 + bb) * HnB >= lo) colw[(int64_t)(b0 + bb) * nw + (x - bb * nw)] = word;
+    }
+  }
+  for (int k = t; k < K; k += kScanThreads) hk[k] = 0;
+  __syncthreads();
+  int L = 0;
+#pragma unroll
+  for (int u = 0; u < kCountWords; ++u) {
+    if (u < nw) {
+      const uint64_t cc = cols != nullptr ? cw[(b - b0) * nw + u] : narrow ? ~0ull : 0ull;
+      const uint64_t m = narrow ? w[u] & cc : (flag ? ~0ull : w[u] | cc);
+      L += __popcll(m & valid_bits(u, nB, nw));
+    }
+  }
+  if (narrow && rows != nullptr && !flag) L = -1;  // left out
+  if (on) {
+    len[r] = L;
+    atomicAdd(&hk[sort_key(L, nB)], 1);
+  }
+  int total;
+  const int ex = block_excl_scan(on ? max(L, 0) : 0, sh, &total);  // ends with a barrier
+  if (on) rloc[r] = ex;
+  for (int k = t; k < K; k += kScanThreads) hist[(int64_t)c * K + k] = hk[k];
+  if (t == 0) csum[c] = total;
+}
+
 // Up to REGS chunks a key's counts stay in registers (one round trip; REGS
 // >= G, the smallest of 4, 8, 16, 32); beyond, they are read sixteen at a
 // time.
@@ -835,10 +897,12 @@ size_t compact_scratch_bytes(int64_t R, int nB) {
 // row_ptr and order from the list lengths, then col_idx by `fill` (built by
 // make_fill from the chunk offsets, the in-chunk prefixes and the chunks);
 // sort_scratch: the part of compact_scratch_bytes after the lengths.
-template <class MakeFill>
+// hist_launch(G, ch, hist, csum, rloc) launches the histograms.
+template <class HistLaunch, class MakeFill>
 static hipError_t launch_sort_fill(const int32_t *len, int64_t R, int nB, int32_t *row_ptr,
                                    int32_t *order, int32_t *n_active, void *sort_scratch,
-                                   int64_t group_rows, const MakeFill &make_fill, hipStream_t s) {
+                                   int64_t group_rows, const HistLaunch &hist_launch,
+                                   const MakeFill &make_fill, hipStream_t s) {
   if (R < 1) return hipErrorInvalidValue;  // G >= 1 below
   const Chunks ch = make_chunks(R, group_rows);
   const int ngroups = n_groups(ch);
@@ -858,13 +922,11 @@ static hipError_t launch_sort_fill(const int32_t *len, int64_t R, int nB, int32_
   int32_t *gtot = reinterpret_cast<int32_t *>(p);
   const auto fill = make_fill(csum, rloc, ch);
   using Fill = std::decay_t<decltype(fill)>;
-  const size_t hl = (size_t)K * sizeof(int32_t);
   const size_t pl = (size_t)K * kSortWaves * sizeof(int32_t);
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&place_fill_kernel<Fill>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(sort_hist_kernel, dim3((unsigned)G), dim3(kScanThreads), hl, s, len, ch, nB, hist,
-                     csum, rloc);
+  hist_launch(G, ch, hist, csum, rloc);
   const size_t gl = (size_t)ngroups * (nB + 2) * sizeof(int32_t);
   if (K <= kScanThreads && G <= 32 && gl <= kScanFastLds) {
     auto scan = G <= 4 ? sort_scan_fast_kernel<4> : G <= 8 ? sort_scan_fast_kernel<8>
@@ -883,6 +945,14 @@ static hipError_t launch_sort_fill(const int32_t *len, int64_t R, int nB, int32_
   hipLaunchKernelGGL(place_fill_kernel<Fill>, dim3((unsigned)(G + fill_groups)), dim3(kScanThreads),
                      pl, s, len, ch, nB, G, hist, csum, rloc, row_ptr, order, fill);
   return hipGetLastError();
+}
+
+// The histograms of given lengths.
+static auto hist_of_lengths(const int32_t *len, int nB, hipStream_t s) {
+  return [=](int G, Chunks ch, int32_t *hist, int32_t *csum, int32_t *rloc) {
+    hipLaunchKernelGGL(sort_hist_kernel, dim3((unsigned)G), dim3(kScanThreads), (size_t)(nB + 2) * sizeof(int32_t),
+                       s, len, ch, nB, hist, csum, rloc);
+  };
 }
 
 // Rows of at most `words` words together, in one head group.
@@ -913,6 +983,7 @@ hipError_t launch_compact(const uint8_t *mask, int64_t R, int nB, int64_t group_
   do {                                                                                           \
     hipLaunchKernelGGL(count_kernel<NU>, dim3(g), dim3(256), 0, s, mask, R, nB, len);            \
     return launch_sort_fill(len, R, nB, row_ptr, order, nullptr, sort_scratch, group_rows,       \
+                            hist_of_lengths(len, nB, s),                                         \
                             [&](const int32_t *coff, const int32_t *rloc, Chunks ch) {           \
                               return FillBytes<NU>{mask, R, nB, coff, rloc, ch, col_idx};        \
                             },                                                                   \
@@ -964,18 +1035,33 @@ hipError_t launch_compact_bits(const uint64_t *bits, int B, int H, int nB, int64
                                hipStream_t s) {
   const int64_t R = (int64_t)B * H * nB;
   int32_t *len = static_cast<int32_t *>(scratch);
-  uint64_t *colw = nullptr;
-  hipError_t e;
-  if (cols != nullptr) {
-    // the column flags of each batch entry, packed once like a mask row
-    colw = reinterpret_cast<uint64_t *>(static_cast<char *>(scratch) + compact_scratch_bytes(R, nB));
-    if ((e = launch_pack(cols, B, nB, colw, s)) != hipSuccess) return e;
-  }
   const int nw = (nB + 63) / 64;  // nB <= 2048
   const int HnB = H * nB;
-  if (few_rows(R, nB, group_rows, kSmallBitsWords))
+  // the column flags of each batch entry, packed once like a mask row
+  uint64_t *colw = cols == nullptr ? nullptr
+                                   : reinterpret_cast<uint64_t *>(static_cast<char *>(scratch) + compact_scratch_bytes(R, nB));
+  void *sort_scratch = static_cast<char *>(scratch) + align_up((size_t)R * sizeof(int32_t));
+  const auto make_fill = [&](const int32_t *coff, const int32_t *rloc, Chunks ch) {
+    return FillBits{bits, (int)R, nB, HnB, rows, colw, narrow, coff, rloc, ch, col_idx};
+  };
+  const bool few = few_rows(R, nB, group_rows, kSmallBitsWords);
+  if (!few && nw <= kCountWords) {
+    // a chunk's rows lie in at most (kChunk - 1) / HnB + 2 batch entries
+    const size_t lds = (cols == nullptr ? 0 : (size_t)((kChunk - 1) / HnB + 2) * nw * sizeof(uint64_t)) +
+                       (size_t)(nB + 2) * sizeof(int32_t);
+    return launch_sort_fill(len, R, nB, row_ptr, order, n_active, sort_scratch, group_rows,
+                            [&](int G, Chunks ch, int32_t *hist, int32_t *csum, int32_t *rloc) {
+                              hipLaunchKernelGGL(sort_hist_bits_kernel, dim3((unsigned)G), dim3(kScanThreads), lds,
+                                                 s, bits, ch, nB, HnB, rows, cols, narrow, colw, len, hist, csum,
+                                                 rloc);
+                            },
+                            make_fill, s);
+  }
+  hipError_t e;
+  if (cols != nullptr && (e = launch_pack(cols, B, nB, colw, s)) != hipSuccess) return e;
+  if (few)
     return launch_small(SmallBits{bits, rows, colw, narrow}, R, nB, HnB, row_ptr, col_idx, order, n_active, s);
-  int G = 1;
+  int G = 8;  // nw > kCountWords here
   while (G < nw) G <<= 1;
   const unsigned gc = (unsigned)((R + 4 * (64 / G) - 1) / (4 * (64 / G)));
   switch (G) {
@@ -984,16 +1070,12 @@ hipError_t launch_compact_bits(const uint64_t *bits, int B, int H, int nB, int64
     hipLaunchKernelGGL(count_bits_kernel<GG>, dim3(gc), dim3(256), 0, s, bits, (int)R, nB, HnB,   \
                        rows, colw, narrow, len);                                                  \
     break;
-    CARNATOR_G(1) CARNATOR_G(2) CARNATOR_G(4) CARNATOR_G(8) CARNATOR_G(16) CARNATOR_G(32)
+    CARNATOR_G(8) CARNATOR_G(16) CARNATOR_G(32)
 #undef CARNATOR_G
     default: return hipErrorInvalidValue;
   }
-  return launch_sort_fill(len, R, nB, row_ptr, order, n_active,
-                          static_cast<char *>(scratch) + align_up((size_t)R * sizeof(int32_t)), group_rows,
-                          [&](const int32_t *coff, const int32_t *rloc, Chunks ch) {
-                            return FillBits{bits, (int)R, nB, HnB, rows, colw, narrow, coff, rloc, ch, col_idx};
-                          },
-                          s);
+  return launch_sort_fill(len, R, nB, row_ptr, order, n_active, sort_scratch, group_rows,
+                          hist_of_lengths(len, nB, s), make_fill, s);
 }
 
 }  // namespace carnator

@@ -187,3 +187,33 @@ def test_compaction_of_few_rows(batch, heads, nb, density):
         want = oracle.compact_restricted(one, act, ctx)
         same(got[:3], want[:3])
         assert int(got[3].item()) == want[3]
+
+
+# Lists from packed rows counted beside the sort's histograms (up to four words
+# a row, more rows than one launch takes) and by a launch of their own, with
+# chunks of rows that span many batch entries and entries that span chunks.
+@pytest.mark.parametrize("batch,heads,nb", [(1, 257, 1), (1100, 1, 1), (300, 1, 5), (40, 1, 30), (3, 7, 64), (2, 9, 65),
+                                            (1, 3, 193), (2, 5, 256), (1, 2, 257), (2, 5, 300)])
+def test_compaction_from_bits_count(batch, heads, nb):
+    rng = np.random.default_rng(nb + batch)
+    m = (rng.random((batch, heads, nb, nb)) < 0.3).astype(np.uint8)
+    m[0, 0, nb // 2] = 0
+    packed = oracle.pack_mask(m)
+    if nb % 64:
+        packed[..., -1] |= np.uint64(1) << np.uint64(63)  # an unused bit: ignored
+    bits = torch.as_tensor(packed.view(np.int64), device=DEV)
+    rows = (rng.random((batch, nb)) < 0.3).astype(np.uint8)
+    cols = (rng.random((batch, nb)) < 0.2).astype(np.uint8) * np.uint8(7)
+    group = P.order_group_heads(batch, heads, nb)
+
+    def same(got, want):
+        for a, b in zip(got, want):
+            np.testing.assert_array_equal(a.cpu().numpy()[:len(b)], b)
+
+    for r, c in ((None, None), (rows, None), (None, cols), (rows, cols)):
+        same(P.compact_block_mask_bits(bits, r, c), oracle.compact_mask(oracle.merge_target_rows(
+            m, np.zeros_like(rows) if r is None else r, c), group_heads=group))
+    ctx = np.maximum(rows, cols)
+    got, want = P.compact_block_mask_bits_region(bits, rows, ctx), oracle.compact_restricted(m, rows, ctx, group_heads=group)
+    same(got[:3], want[:3])
+    assert int(got[3].item()) == want[3]
