@@ -449,7 +449,7 @@ int carnator_block_sparse_attn_rows(const carnator_view *q, const carnator_view 
  *   lse_a = log sum_{t in A(a)} exp(sigma * q_a . k_t),
  * sigma = scale, or 1/sqrt(head_dim) when scale <= 0.  A row with no kept
  * block gives o = 0 and lse = -inf.  bf16 matrix cores for Q.K^T and P.V,
- * fp32 accumulation and online softmax; O is rounded to bf16.
+ * fp32 accumulation and softmax; O is rounded to bf16.
  *
  *   q, k, v        bf16 views [B, H, N, d]
  *   out            bf16 [B, H, N, d] at element strides out_stride_{b,h,n}

@@ -119,16 +119,17 @@ struct Cfg {
   static_assert(TB % (1024 * WAVES) == 0, "tile split");
 };
 
-// One workgroup per query block, 32 queries per wave, two waves per SIMD.
+// One workgroup per query block, 32 queries per wave, two waves per SIMD at
+// 128-token blocks and d = 128.
 //
 // A wave issues vector instructions while its own MFMAs execute, but two
 // waves sharing a SIMD overlap their MFMA and vector work far less, so the
 // overlap is built into each wave's instruction stream.  Iteration j:
-//   part A: O += V(j-1)^T P(j-1)^T on the matrix cores, interleaved with the
-//           softmax of S(j) (row max, and P for the first 32 keys);
-//   part B: S(j+1) = K(j+1) Q^T, first for keys 0..31 of the stage while P
-//           for keys 32..63 of S(j) is formed, then for keys 32..63 once
-//           those scores have been consumed.
+//   part A: O += V(j-1)^T P(j-1)^T on the matrix cores, interleaved with most
+//           of the exponentials of S(j);
+//   part B: S(j+1) = K(j+1) Q^T, first for keys 0..31 of the stage beside the
+//           last exponentials of S(j), then for keys 32..63, whose scores of
+//           S(j) have been consumed, beside the first of S(j+1).
 // Only P is double-buffered in registers (the scores are reused in place).
 //
 // K and V have two LDS slots each.  Iteration j waits for V(j-1) and K(j+1),
