@@ -43,12 +43,13 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 // the transfer, and the compiler then drains all outstanding loads
 // (vmcnt(0)) before each operand read, which removes the prefetch.  The
 // asm writes M0 and declares it clobbered, so the compiler keeps no value of
-// its own in M0 across a load.
+// its own in M0 across a load; the s_nop is the wait state that a load through
+// M0 needs after a scalar write of it.
 //
 // 16 bytes per lane from base + voff to LDS offset lds_off + 16 * lane; base
 // and lds_off are the same in every lane.
 __device__ inline void dma16(const void *base, unsigned voff, unsigned lds_off) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base),
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base),
                "s"(__builtin_amdgcn_readfirstlane(lds_off))
                : "memory", "m0");
 }
