@@ -207,8 +207,8 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
   // i.e. row +lrow, slot `slot`, which holds chunk slot ^ swz(row).
   // A tile always covers KT rows inside the tensor: a stage reaching past N
   // loads the KT rows ending at N instead (and masks the keys outside the
-  // stage), and when N < KT the rows past N re-read row N - 1.  So one set
-  // of lane offsets serves every tile.
+  // stage, zeroes their V rows), and when N < KT the rows past N re-read row
+  // N - 1.  So one set of lane offsets serves every tile.
   const int lrow = lane / (C::RB / 16), slot = lane % (C::RB / 16);
   unsigned koff[C::LI], voff[C::LI];  // lane offsets of a tile, bytes
 #pragma unroll
@@ -268,6 +268,26 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
   auto mask_tail = [&](f32x16 (&sacc)[MT], int k0) __attribute__((always_inline)) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) mask_tile(sacc, mt, k0);
+  };
+  // Waits for the tiles in flight, the V tile in slot VS among them, whose
+  // stage begins at key k0.  A masked key has P = 0, which an infinite or NaN
+  // value would still turn into NaN, and its row may belong to a key block
+  // that the list does not hold: each wave zeroes those of the rows it loaded.
+  auto wait_v_then_barrier = [&](auto vs_c, int k0) __attribute__((always_inline)) {
+    if (k0 + KT > N) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      int at = lane * 16;           // of this lane in a 1-KiB load
+      asm volatile("" : "+v"(at));  // formed here: ahead of the loop it would keep registers
+#pragma unroll
+      for (int i = 0; i < C::LI; ++i) {
+        const int row = C::RPL * (wave * C::LI + i) + at / C::RB;
+        const int key = min(k0, kmax) + row;
+        if (key < k0 || key >= N)
+          *reinterpret_cast<uint4 *>(lds + (2 + decltype(vs_c)::value) * C::TB + (wave * C::LI + i) * 1024 + at) =
+              make_uint4(0, 0, 0, 0);
+      }
+    }
+    wait_all_then_barrier();
   };
   auto rescale_o = [&]() __attribute__((always_inline)) {
     if (__ballot(alpha != 1.f)) {
@@ -502,11 +522,13 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
     // (first half of block b) and K(2b+2) (first half of block b+1),
     // iteration 2b+1 the second halves.  blk0 / blk1 hold blocks b and b+1;
     // block b+2 is read from the LDS list one pair ahead.
+    int vk0 = 0;  // the first key of the stage whose V is in flight
     auto pair = [&](auto first, int b) __attribute__((always_inline)) {
       const int nxt = list[min(b + 2, L - 1)];
       const bool more = b + 1 < L;
       // even stage j = 2b
-      wait_all_then_barrier();
+      if constexpr (decltype(first)::value) wait_all_then_barrier();
+      else wait_v_then_barrier(I1{}, vk0);
       if constexpr (TRACK && !decltype(first)::value) rescale_o();
       {
         const int kv = blk0 * BS;
@@ -516,10 +538,10 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
                 tile_base(kbase, k.sn, min(kk, kmax)), wdst, blk0 * BS + 2 * KT > N, blk0 * BS + KT);  // S(2b+1)
       }
       // odd stage j = 2b+1
-      wait_all_then_barrier();
+      wait_v_then_barrier(I0{}, blk0 * BS);
       if constexpr (TRACK) rescale_o();
       {
-        const int kv = blk0 * BS + KT;
+        const int kv = vk0 = blk0 * BS + KT;
         const int kk = more ? blk1 * BS + KT : 0;
         iterate(track, T{}, I0{}, I0{}, st, sc, pa, pb, tile_base(vbase, v.sn, min(kv, kmax)), wdst + 3 * C::TB,
                 tile_base(kbase, k.sn, min(kk, kmax)), wdst + C::TB, more && blk1 * BS + KT > N,
@@ -539,7 +561,9 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
         constexpr bool O = decltype(odd)::value;
         using Slot = std::integral_constant<int, O ? 0 : 1>;  // of V(j-1) and K(j+1)
         const int nxt = list[min(j + 3, L - 1)];
-        wait_all_then_barrier();
+        if constexpr (decltype(first)::value) wait_all_then_barrier();
+        else wait_v_then_barrier(Slot{}, vk0);
+        vk0 = blk0 * BS;
         if constexpr (TRACK && !decltype(first)::value) rescale_o();
         const unsigned to = wdst + (O ? C::TB : 0);
         iterate(track, std::integral_constant<bool, !decltype(first)::value>{}, Slot{}, Slot{}, st, sc, O ? pa : pb,
@@ -558,9 +582,9 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
       if (j < L) stage(F{}, T{}, j);
     }
     // P.V of the last stage (odd: V slot 1, P in pb; even: V slot 0, P in pa)
-    wait_all_then_barrier();
-    if constexpr (TRACK) rescale_o();
     auto pv_last = [&](auto vs_c, const u32x4 (&pl)[KT / 16]) __attribute__((always_inline)) {
+      wait_v_then_barrier(vs_c, vk0);
+      if constexpr (TRACK) rescale_o();
 #pragma unroll
       for (int tp = 0; tp < KT / 16; ++tp)
 #pragma unroll

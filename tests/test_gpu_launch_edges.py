@@ -217,3 +217,34 @@ def test_compaction_from_bits_count(batch, heads, nb):
     got, want = P.compact_block_mask_bits_region(bits, rows, ctx), oracle.compact_restricted(m, rows, ctx, group_heads=group)
     same(got[:3], want[:3])
     assert int(got[3].item()) == want[3]
+
+
+# A value that is not finite reaches exactly the queries whose lists hold its
+# key block, also where a stage reaches past the last token: in the block
+# before the ragged one, whose rows such a stage's tile takes in; in the ragged
+# block itself, which a second half-stage past the end takes in again; and with
+# fewer tokens than a stage, where the rows past the end repeat the last one.
+@pytest.mark.parametrize("n,d,bs,token", [(600, 64, 64, 550), (600, 128, 64, 570), (540, 128, 128, 500),
+                                          (540, 64, 128, 480), (540, 128, 128, 520), (540, 64, 128, 539),
+                                          (610, 128, 64, 585), (40, 64, 128, 39), (20, 128, 64, 19), (50, 64, 64, 49)])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_attention_infinite_values_near_the_end(n, d, bs, token, bad):
+    print("attention non-finite value", n, d, bs, token, bad, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(n + d)
+    q, k, v = (torch.randn(1, 1, n, d, generator=g, device=DEV).to(torch.bfloat16) for _ in range(3))
+    clean = v.clone()
+    v[0, 0, token, 7] = bad
+    nb = -(-n // bs)
+    m = np.ones((1, 1, nb, nb), np.uint8)
+    if nb > 1:
+        m[0, 0, ::2, token // bs] = 0
+    holds = torch.arange(n, device=DEV) // bs % 2 == 1 if nb > 1 else torch.ones(n, dtype=torch.bool, device=DEV)
+    dm = torch.as_tensor(m, device=DEV)
+    o, _ = P.block_sparse_attn(q, k, v, dm, bs, return_lse=True)
+    assert torch.equal(o.isfinite(), P.block_sparse_attn(q, k, v, dm, bs).isfinite())
+    o = o[0, 0]
+    hit = torch.isinf(o[:, 7]) if bad == float("inf") else torch.isnan(o[:, 7])
+    assert torch.equal(hit, holds)
+    assert torch.isfinite(o[:, torch.arange(d, device=DEV) != 7]).all()
+    want = P.block_sparse_attn(q, k, clean, dm, bs)[0, 0]
+    assert torch.equal(o[~holds], want[~holds])
