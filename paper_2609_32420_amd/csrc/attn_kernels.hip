@@ -78,6 +78,9 @@ __device__ inline float2 halves(float x) {
 // P may then reach 2^8, harmless in fp32 and bf16, and most stages skip the
 // rescale of the output accumulators.
 constexpr float kRescaleSlack = 8.f;
+// How far (log2 units) a reference below 0 lies above the query's first-stage
+// maximum, and the row sum that such a query may reach.
+constexpr float kLowReference = 32.f, kLowSumMax = 0x1p64f;
 
 // Chunk swizzles (16-byte chunk c of row r sits in slot c ^ swz(r)).
 // K: the 16 lanes of a bank cycle read rows 0..15 (permuted) at one chunk.
@@ -137,19 +140,26 @@ struct Cfg {
 // meets the other waves (after which K(j) and V(j-2) are no longer read) and
 // issues V(j) and K(j+2) into those slots.
 //
-// The softmax has one reference per query, the largest score of its first
-// stage or 0 if that is less: no score waits for its stage's maximum, there
-// is no rescaling, and P is formed evenly under all of the iteration's MFMAs
-// instead of after the maximum.  P, the row sums and O then range over
-// fp32's (bf16's) exponents at the precision they had, and with a reference
-// of at least 0 the fma rounds x - r no coarser than x itself where x carries
-// weight.  A workgroup that finds a row sum outside [2^-40, 2^100] or an
-// output that is not finite walks its row again under running maxima
-// (walk<true>: a grown maximum only records alpha, and O is rescaled at the
-// start of the next iteration, since the P.V in flight belongs to the
-// old one).  Measured against running maxima throughout: 48 heads x 17,776
-// tokens, d = 64, with the LSE 2027 -> 1851 us; lists at d = 128: 12 heads x
-// 32,760 tokens 1673 -> 1618 us, 24 heads x 119,056 tokens 23.8 -> 22.6 ms.
+// The softmax has one reference r per query: the largest score m of its first
+// stage, or min(m + 32, 0) if m is below 0.  No score waits for its stage's
+// maximum, there is no rescaling, and P is formed evenly under all of the
+// iteration's MFMAs instead of after the maximum.  P, the row sums and O then
+// range over fp32's (bf16's) exponents at the precision they had.  With r of
+// at least 0 the fma rounds x - r no coarser than x itself where x carries
+// weight; with scores that all lie lower (a common part of Q and K shifts
+// every score of a query) x - r stays within -32 .. 64 there and rounds by
+// 2^-19 at most.  A workgroup that finds a row sum outside [2^-40, 2^100]
+// (2^64 where r < 0) or an output that is not finite walks its row again
+// under running maxima (walk<true>: a grown maximum only records alpha, and O
+// is rescaled at the start of the next iteration, since the P.V in flight
+// belongs to the old one).  That takes a query with scores about 100 above its
+// first stage, or inputs that are not finite, and doubles the time of the row
+// (every row of 12 heads x 32,760 tokens, 40 % of the pairs: 2601 -> 5317 us;
+// of 48 x 17,776 at d = 64: 1667 -> 3540); a shift of every score by -40 nats
+// costs nothing.  Measured against running maxima throughout: 48 heads x
+// 17,776 tokens, d = 64, with the LSE 2027 -> 1851 us; lists at d = 128: 12
+// heads x 32,760 tokens 1673 -> 1618 us, 24 heads x 119,056 tokens 23.8 ->
+// 22.6 ms.
 // At d = 64 the kernel is held to 168 registers, so three workgroups share a
 // CU (their LDS, 3 x 40 KB, fits): with half the MFMAs per score of d = 128
 // it is bound by its vector work, which a third wave per SIMD overlaps better.
@@ -507,13 +517,12 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
     if (blk0 * BS + KT > N) mask_tail(sc, blk0 * BS);
     Soft st{-INFINITY, -INFINITY, 0.f, 0.f, 0.f, 0.f, 0.f};
     if constexpr (!TRACK) {
-      // the query's reference: the largest score of its first stage, at
-      // least 0
+      // the query's reference from the largest score of its first stage
 #pragma unroll
       for (int x = 0; x < SC; x += 4) sm_max(st, sc, x);
       const float2 hv = halves(__builtin_fmaxf(st.m0, st.m1));
       const float m = __builtin_fmaxf(hv.x, hv.y) * c2;
-      mrun = st.msub = __builtin_fmaxf(m, 0.f);
+      mrun = st.msub = m < 0.f ? __builtin_fminf(m + kLowReference, 0.f) : m;
 #pragma unroll
       for (int c = 0; c < XE; ++c) sm_exp(st, sc, pa, 2 * c);
     }
@@ -602,9 +611,9 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
 
   if (e1 > e0) {
     walk(std::false_type{});
-    // A query whose scores lie far from its reference (a row sum outside
-    // [2^-40, 2^100], or an output that is not finite), or whose inputs are
-    // not finite: the workgroup walks the row again under running maxima.
+    // A query whose scores lie far from its reference (a row sum outside its
+    // range, or an output that is not finite), or whose inputs are not
+    // finite: the workgroup walks the row again under running maxima.
     float t0 = 0.f, t1 = 0.f;
 #pragma unroll
     for (int mo = 0; mo < D / 32; ++mo)
@@ -615,7 +624,7 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
       }
     const float2 lw = halves(lrun);
     const float lsum = lw.x + lw.y;
-    const bool fine = lsum >= 0x1p-40f && lsum <= 0x1p100f && t0 + t1 == 0.f;
+    const bool fine = lsum >= 0x1p-40f && lsum <= (mrun < 0.f ? kLowSumMax : 0x1p100f) && t0 + t1 == 0.f;
     volatile int *flag = reinterpret_cast<int *>(lds + C::LIST) + kMaxListBlocks;
     if (__ballot(!fine) != 0 && lane == 0) *flag = 1;
     wait_all_then_barrier();

@@ -90,10 +90,12 @@ def test_exact_mass_reference_and_workgroup_sizes(kind, n, heads, d, bs):
 
 
 # Attention around the one reference per query (the largest score of the first
-# 64 keys, at least 0): logits whose later keys exceed it by 2^60 (in range), by more
-# than 2^100 or 2^128 (the workgroup walks the row again under running
-# maxima), all 30 below 0 (in range) or 250 (walked again), or mixed between the workgroup's queries; values
-# near the largest bf16, whose products overflow beside a grown reference.
+# stage's 32 or 64 keys, below 0 raised by 32 up to 0): logits whose later keys
+# exceed it by 2^60 (in range), by more than 2^100 or 2^128 (the workgroup
+# walks the row again under running maxima), all 30 below 0 (reference 0) or
+# 250 (a reference below 0), or mixed between the workgroup's queries (walked
+# again); values near the largest bf16, whose products overflow beside a grown
+# reference.
 # Logits here reach 600 in log2 units and carry up to D / 16 + 1 fp32
 # roundings of 2^-24 of that each: 3e-4 relative on a probability, far below
 # the bf16 rounding of P and O (2^-8 each) that the tolerances are for.
@@ -248,3 +250,75 @@ def test_attention_infinite_values_near_the_end(n, d, bs, token, bad):
     assert torch.isfinite(o[:, torch.arange(d, device=DEV) != 7]).all()
     want = P.block_sparse_attn(q, k, clean, dm, bs)[0, 0]
     assert torch.equal(o[~holds], want[~holds])
+
+
+def _shifted(heads, n, d, base, rise, seed=0):
+    """q, k, v with base + rise t / n (log2 units) added to every logit of key t."""
+    g = torch.Generator(device=DEV).manual_seed(n + d + seed)
+    q, k, v = (torch.randn(1, heads, n, d, generator=g, device=DEV) for _ in range(3))
+    q[..., 0] = 20.0
+    t = torch.arange(n, device=DEV, dtype=torch.float32)
+    k[..., 0] = d ** 0.5 / 20.0 * 0.6931 * (base + rise * t / n)
+    return (x.to(torch.bfloat16) for x in (q, k, v))
+
+
+# Logits below 0: every one lower by the same amount (either side of the line
+# below which a query's reference follows its scores), and scores that climb
+# from there by less than a reference below 0 allows, or by more (the workgroup
+# starts over).  Logits reach 140 log2 units over up to D / 16 + 2 roundings of
+# 2^-24 of that each, and x - r rounds by 2^-19 at most: 9e-5 in log2 units,
+# 6e-5 in the LSE and on a mass relative to its row's largest.
+_CLIMBS = [(-20.0, 0.0), (-31.0, 0.0), (-35.0, 0.0), (-60.0, 0.0), (-110.0, 0.0), (-60.0, 40.0), (-60.0, 80.0),
+           (-100.0, 80.0), (-100.0, 90.0), (-100.0, 120.0), (-20.0, 130.0)]
+
+
+@pytest.mark.parametrize("base,rise", _CLIMBS)
+@pytest.mark.parametrize("n,d,bs", [(1000, 128, 128), (1000, 64, 128), (690, 128, 64), (690, 64, 64), (50, 64, 64)])
+def test_attention_reference_below_zero(base, rise, n, d, bs):
+    print("attention reference", base, rise, n, d, bs, flush=True)
+    q, k, v = _shifted(2, n, d, base, rise)
+    nb = -(-n // bs)
+    m = np.ones((1, 2, nb, nb), np.uint8)
+    dm = torch.as_tensor(m, device=DEV)
+    o, lse = P.block_sparse_attn(q, k, v, dm, bs, return_lse=True)
+    assert torch.equal(o, P.block_sparse_attn(q, k, v, dm, bs))
+    ro, rl = oracle.block_sparse_attention(oracle.to_f64(q), oracle.to_f64(k), oracle.to_f64(v), m, bs)
+    got = o.double().cpu().numpy()
+    assert np.abs(got - ro).max() <= 2e-2
+    assert np.linalg.norm(got - ro) <= 5e-3 * np.linalg.norm(ro)
+    err = float(np.abs(lse.double().cpu().numpy() - rl).max())
+    print("lse error", err)
+    assert err <= 6e-5
+
+
+def _times(calls, repeats=15):
+    """Median time of each call (us), the calls taken in turn."""
+    took = [[] for _ in calls]
+    for i in range(repeats + 3):
+        for c, t in zip(calls, took):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            c()
+            b.record()
+            b.synchronize()
+            if i >= 3:
+                t.append(1e3 * a.elapsed_time(b))
+    return [float(np.median(t)) for t in took]
+
+
+# One amount taken from every logit leaves the softmax as it is, and costs
+# nothing: a query's reference follows its scores down.  Nor do scores that
+# climb from far below 0 to about 0.  A second walk of the row would be twice
+# the time.
+@pytest.mark.parametrize("n,d,bs", [(6000, 128, 128), (6000, 64, 128), (6000, 128, 64), (6000, 64, 64)])
+@pytest.mark.parametrize("base,rise", [(-20.0, 0.0), (-60.0, 0.0), (-300.0, 0.0), (-60.0, 60.0), (-90.0, 80.0)])
+def test_attention_time_of_shifted_logits(n, d, bs, base, rise):
+    heads, nb = 24, -(-n // bs)
+    lists = P.compact_block_mask(torch.ones(1, heads, nb, nb, dtype=torch.uint8, device=DEV))
+    calls = []
+    for shift, up in ((0.0, 0.0), (base, rise)):
+        q, k, v = _shifted(heads, n, d, shift, up)
+        calls.append(lambda q=q, k=k, v=v: P.block_sparse_attn_lists(q, k, v, lists, bs))
+    plain, shifted = _times(calls)
+    print("attention", n, d, bs, base, rise, "plain %.1f us, shifted %.1f us" % (plain, shifted), flush=True)
+    assert shifted <= 1.35 * plain
