@@ -658,8 +658,12 @@ bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, i
     if constexpr (WITH_LSE) {
       const float2 eh = halves(lexact);
       const float etot = eh.x + eh.y;
-      if (hh == 0)
-        lse[(int64_t)bh * N + qtok] = etot > 0.f ? (mrun + __log2f(etot)) * 0.69314718055994531f : -INFINITY;
+      // reference, exponent and log2 of the sum's mantissa in fp64: the first
+      // two can be large where the LSE is small, and log2(etot) would round
+      // by its size
+      const double l2 = (double)mrun + (double)__builtin_amdgcn_frexp_expf(etot) +
+                        (double)__log2f(__builtin_amdgcn_frexp_mantf(etot));
+      if (hh == 0) lse[(int64_t)bh * N + qtok] = etot > 0.f ? (float)(l2 * 0.69314718055994531) : -INFINITY;
     }
   }
 }

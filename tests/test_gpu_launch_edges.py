@@ -322,3 +322,23 @@ def test_attention_time_of_shifted_logits(n, d, bs, base, rise):
     plain, shifted = _times(calls)
     print("attention", n, d, bs, base, rise, "plain %.1f us, shifted %.1f us" % (plain, shifted), flush=True)
     assert shifted <= 1.35 * plain
+
+
+# A reference and a row sum that are both large beside the LSE: the keys of the
+# first stage lie 60 to 84 log2 units below 0, four later ones at exactly 0, so
+# the LSE is log 4.  Roundings of 2^-24: one in the exponential (two as an ulp),
+# three in the sum, two in the mantissa's log2, and one of an LSE of 1.4: 8 of
+# 6e-8 at most.
+@pytest.mark.parametrize("d,bs", [(128, 128), (64, 128), (128, 64), (64, 64)])
+def test_attention_lse_beside_a_large_reference(d, bs):
+    n = 68
+    q, k = torch.zeros(1, 1, n, d, device=DEV), torch.zeros(1, 1, n, d, device=DEV)
+    q[0, 0, :, 0] = 20.0 + 0.125 * torch.arange(n, device=DEV) % 8.0
+    k[0, 0, :64, 0] = -3.0 * 0.6931 * d ** 0.5
+    nb = -(-n // bs)
+    q, k = q.to(torch.bfloat16), k.to(torch.bfloat16)
+    _, lse = P.block_sparse_attn(q, k, torch.ones_like(q), torch.ones(1, 1, nb, nb, dtype=torch.uint8, device=DEV), bs,
+                                 return_lse=True)
+    err = float((lse.double() - np.log(4.0)).abs().max())
+    print("lse error", d, bs, err)
+    assert err <= 5e-7
