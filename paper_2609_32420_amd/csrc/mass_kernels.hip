@@ -19,14 +19,18 @@
 // The records are block-major ([bh][j][a]) so a wave's 64 queries write 256
 // contiguous bytes.
 //
-// The reference is the maximum over the query's first 32 keys, at least 0: no
-// running maximum and no rescaling, a score costs one fma, one exp2 and one
-// add.  2^(x - r) spans 2^-126 .. 2^127 whatever r is, so the sums are as
-// precise as with the row maximum; with r >= 0 the fma rounds x - r no
-// coarser than x itself for every x that carries mass.  A query whose total
-// leaves [2^-40, 2^100] (scores more than 100 log2 units above its first
-// keys, or all below -40) makes its workgroup start over with the true row
-// maxima, taken in a pass of their own.
+// The reference is the maximum m over the query's first 32 keys, or
+// min(m + 32, 0) if m is below 0: no running maximum and no rescaling, a score
+// costs one fma, one exp2 and one add.  2^(x - r) spans 2^-126 .. 2^127
+// whatever r is, so the sums are as precise as with the row maximum; with
+// r >= 0 the fma rounds x - r no coarser than x itself for every x that
+// carries mass, and with scores that all lie lower x - r stays within
+// -32 .. 64 there.  A query whose total leaves [2^-40, 2^100] (2^64 if a query
+// of its wave has r < 0; scores about 100 log2 units above its first keys), or
+// with inputs that are not finite, makes its workgroup start over with the
+// true row maxima, taken in a pass of their own: three passes over K for one
+// (every workgroup of 12 heads x 32,760 tokens: 2.95 -> 7.9 ms, of 48 x 17,776
+// at d = 64 2.57 -> 6.2).  A shift of every score by -40 nats costs nothing.
 //
 // Bound: the vector work beside the MFMAs (per 32-key tile and set D / 16
 // MFMAs against 16 fma, 16 exp2 and 16 adds).  12 heads of 32,760 tokens, d =
@@ -78,6 +82,11 @@ __device__ inline float pair_sums(float a, float b) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
+
+// How far (log2 units) a reference below 0 lies above the query's first
+// maximum, and the total that such a query may reach.
+constexpr float kLowReference = 32.f;
+constexpr double kLowTotalMax = 0x1p64;
 
 template <int D, int BS, int NW>
 struct MassCfg {
@@ -216,9 +225,13 @@ mass_pass_kernel(View q, View k, int H, int N, int nB, int bh0, float c2,
 #pragma unroll
     for (int t = 0; t < F; ++t) mfma(accA, q0, t), mfma(accB, q1, t);
     if (round == 0) {
-      refA = fmaxf(ceilf(tile_max(accA) * c2), 0.f);
-      refB = fmaxf(ceilf(tile_max(accB) * c2), 0.f);
+      const float mA = ceilf(tile_max(accA) * c2), mB = ceilf(tile_max(accB) * c2);
+      refA = mA < 0.f ? fminf(mA + kLowReference, 0.f) : mA;
+      refB = mB < 0.f ? fminf(mB + kLowReference, 0.f) : mB;
     }
+    // whether a query of the wave has a reference below 0 (scalar: kept per
+    // lane it would cost vector registers through the loop)
+    const bool low = __ballot(fminf(refA, refB) < 0.f) != 0;
     l = 0.0;
     float psA0, psA1, psB0, psB1;
     // scores [v, v + SPS) of a tile
@@ -276,7 +289,8 @@ mass_pass_kernel(View q, View k, int H, int N, int nB, int bh0, float c2,
     };
     for (int j = 0; j < nB - 1; ++j) block(std::false_type{}, j);
     block(std::true_type{}, nB - 1);  // only the last block can be partial
-    const bool bad = mine && !(l >= 0x1p-40 && l <= 0x1p100);
+    const double most = low ? kLowTotalMax : 0x1p100;
+    const bool bad = mine && !(l >= 0x1p-40 && l <= most);
     if (round == 1 || !__syncthreads_or(bad)) break;
   }
   if (mine) total[(int64_t)bc * N + aw + lane] = (float)l;

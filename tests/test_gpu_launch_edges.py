@@ -55,9 +55,9 @@ def test_selection_ties_across_words(nb, first, last, keep):
 
 
 # The exact masses around the pass's fixed reference: logits whose later keys
-# exceed the first 32 by more than 2^100 or whose keys all lie far below 0
-# (both make a workgroup start over with the row maxima), beside ordinary
-# ones; grids of 4- and of 8-wave workgroups.  Scores are fp32 sums of D bf16
+# exceed the first 32 by more than 2^100 (the workgroup starts over with the row
+# maxima) or whose keys all lie far below 0, beside ordinary ones; grids of 4-
+# and of 8-wave workgroups.  Scores are fp32 sums of D bf16
 # products in 3 to 8 roundings of 2^-24 |x|: with |x| up to 600 log2 units a
 # mass is off by 600 * 8 * 6e-8 = 3e-4 relative at most.
 @pytest.mark.parametrize("kind", ["plain", "rising", "low", "mixed"])
@@ -291,6 +291,20 @@ def test_attention_reference_below_zero(base, rise, n, d, bs):
     assert err <= 6e-5
 
 
+@pytest.mark.parametrize("base,rise", _CLIMBS)
+@pytest.mark.parametrize("n,heads,d,bs", [(700, 2, 128, 128), (321, 2, 64, 64), (1030, 90, 64, 64)])
+def test_exact_mass_reference_below_zero(base, rise, n, heads, d, bs):
+    print("exact mass reference", base, rise, n, heads, d, bs, flush=True)
+    q, k, _ = _shifted(heads, n, d, base, rise)
+    mass = P.block_mass_exact(q, k, bs).cpu().numpy()
+    nb = -(-n // bs)
+    for (h, i) in sorted({(h, i) for h in (0, heads - 1) for i in (0, nb // 2, nb - 1)}):
+        want = oracle.exact_block_mass(oracle.to_f64(q[:, h:h + 1]), oracle.to_f64(k[:, h:h + 1]), bs,
+                                       rows=[(0, 0, i)])[0, 0, i]
+        assert np.abs(mass[0, h, i] - want).max() <= 6e-5 * want.max(), (h, i)
+    np.testing.assert_allclose(mass.sum(-1), 1.0, atol=1e-6)
+
+
 def _times(calls, repeats=15):
     """Median time of each call (us), the calls taken in turn."""
     took = [[] for _ in calls]
@@ -321,6 +335,18 @@ def test_attention_time_of_shifted_logits(n, d, bs, base, rise):
         calls.append(lambda q=q, k=k, v=v: P.block_sparse_attn_lists(q, k, v, lists, bs))
     plain, shifted = _times(calls)
     print("attention", n, d, bs, base, rise, "plain %.1f us, shifted %.1f us" % (plain, shifted), flush=True)
+    assert shifted <= 1.35 * plain
+
+
+@pytest.mark.parametrize("n,d,bs", [(6000, 128, 128), (6000, 64, 64)])
+@pytest.mark.parametrize("base,rise", [(-20.0, 0.0), (-60.0, 0.0), (-300.0, 0.0), (-60.0, 60.0), (-90.0, 80.0)])
+def test_exact_mass_time_of_shifted_logits(n, d, bs, base, rise):
+    calls = []
+    for shift, up in ((0.0, 0.0), (base, rise)):
+        q, k, _ = _shifted(24, n, d, shift, up)
+        calls.append(lambda q=q, k=k: P.block_mass_exact(q, k, bs))
+    plain, shifted = _times(calls)
+    print("exact mass", n, d, bs, base, rise, "plain %.1f us, shifted %.1f us" % (plain, shifted), flush=True)
     assert shifted <= 1.35 * plain
 
 
