@@ -221,6 +221,36 @@ def test_compaction_from_bits_count(batch, heads, nb):
     assert int(got[3].item()) == want[3]
 
 
+# The same from a row order of several head groups: chunks that start at a
+# group's first row, partial chunks inside the grid, and batch entries that
+# begin in the middle of a group or of a chunk.
+@pytest.mark.parametrize("batch,heads,nb,attn", [(1, 40, 256, (32760, 128, 128)), (2, 24, 256, (32760, 128, 128)),
+                                                 (3, 40, 193, (193 * 128 - 7, 128, 128)),
+                                                 (1, 260, 129, (129 * 64, 64, 64))])
+def test_compaction_from_bits_count_of_head_groups(batch, heads, nb, attn):
+    rng = np.random.default_rng(nb + heads)
+    m = (rng.random((batch, heads, nb, nb)) < 0.3).astype(np.uint8)
+    m[0, 0, nb // 2] = 0
+    bits = torch.as_tensor(oracle.pack_mask(m).view(np.int64), device=DEV)
+    rows = (rng.random((batch, nb)) < 0.3).astype(np.uint8)
+    cols = (rng.random((batch, nb)) < 0.2).astype(np.uint8)
+    group = P.order_group_heads(batch, heads, nb, attn=attn)
+    assert group < batch * heads
+
+    def same(got, want):
+        for a, b in zip(got, want):
+            np.testing.assert_array_equal(a.cpu().numpy()[:len(b)], b)
+
+    for r, c in ((None, None), (rows, cols)):
+        same(P.compact_block_mask_bits(bits, r, c, attn=attn), oracle.compact_mask(oracle.merge_target_rows(
+            m, np.zeros_like(rows) if r is None else r, c), group_heads=group))
+    ctx = np.maximum(rows, cols)
+    got = P.compact_block_mask_bits_region(bits, rows, ctx, attn=attn)
+    want = oracle.compact_restricted(m, rows, ctx, group_heads=group)
+    same(got[:3], want[:3])
+    assert int(got[3].item()) == want[3]
+
+
 # A value that is not finite reaches exactly the queries whose lists hold its
 # key block, also where a stage reaches past the last token: in the block
 # before the ragged one, whose rows such a stage's tile takes in; in the ragged
