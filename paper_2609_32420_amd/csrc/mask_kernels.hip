@@ -252,17 +252,20 @@ constexpr int sel_prev(int e) {
 // 16 g + 4 k .. 16 g + 4 k + 3 of key block i (one 32-byte piece of its kbar
 // row) and feeds channel 16 g + 4 k + t to step t, and the query side takes
 // its channels in the same order.  With R = 8 the upper half of the tile
-// repeats row R - 1 and is not stored.  Phase 2: wave w selects rows w,
-// w + W, ... of the workgroup (E = positions per lane, 64 E >= nB).
+// repeats row R - 1 and is not stored.  Phase 2: wave w selects row w of the
+// workgroup (E = positions per lane, 64 E >= nB).
 //
 // Bound: at nB = 591 (40 heads) 192 us, was 244 us: the score tiles with
 // their kbar loads (0.9 GB through the L2) 119 us, 74 us of it the fp64
 // matrix cores (2048 cycles a tile), and the selection 73 us of dependent
-// vector work, ~1330 vector instructions a row; one workgroup per CU (its
-// LDS), so the two do not overlap.  The gain is one row per wave on 16 waves
-// (244 -> 215 us) and a selection free of branches per position: rows padded to 64 E
-// so that every logit is loaded at once, exp_neg, and the tie ranks taken on
-// whole 64-bit words.  At nB <= 256 one workgroup's latency (20 us).
+// vector work, ~1330 vector instructions a row; one workgroup per CU, so the
+// two do not overlap: by its LDS from 385 blocks on, below by the registers of
+// its 16 waves (75 a lane at d = 64 and 119 at 128, where two would need 64).
+// The gain is one row per wave on 16 waves (244 -> 215 us) and a selection
+// free of branches per position: rows padded to 64 E so that every logit is
+// loaded at once, exp_neg, and the tie ranks taken on whole 64-bit words.  At
+// nB <= 256 one workgroup's latency (20 us), twice that where there are more
+// workgroups than CUs (48 heads of 139 blocks: 432).
 // MASS: the rows are given, as block masses [BH][nB][nB] at qbar (kbar and
 // sigma unused): phase 1 copies the workgroup's rows into LDS and phase 2
 // selects on the masses themselves instead of the softmax of logits.
@@ -300,12 +303,12 @@ __global__ void __launch_bounds__(64 * W) select_kernel(const double *__restrict
 
   if constexpr (MASS) {
     const double *src = qbar + ((int64_t)bh * nB + r0) * nB;
-    for (int r = wave; r < nr; r += W)
+    if (wave < nr)
 #pragma unroll
       for (int u = 0; u < E; ++u) {
         const int p = u * 64 + lane;
-        const double m = src[r * nB + min(p, nB - 1)];
-        sc[r * NP + p] = p < nB ? m : -INFINITY;
+        const double m = src[wave * nB + min(p, nB - 1)];
+        sc[wave * NP + p] = p < nB ? m : -INFINITY;
       }
     __syncthreads();
   } else {
@@ -324,8 +327,8 @@ __global__ void __launch_bounds__(64 * W) select_kernel(const double *__restrict
         qs[r * QS + c] = sv[i];
       }
     }
-    for (int r = wave; r < nr; r += W)
-      for (int p = nB + lane; p < NP; p += 64) sc[r * NP + p] = -INFINITY;
+    if (wave < nr)
+      for (int p = nB + lane; p < NP; p += 64) sc[wave * NP + p] = -INFINITY;
     __syncthreads();
     {
       typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -392,7 +395,7 @@ __global__ void __launch_bounds__(64 * W) select_kernel(const double *__restrict
   // registers; the vector work per step is one compare and add per position
   // and one wave sum.
   const ExpCoef ec = exp_coef();
-  for (int r = wave; r < nr; r += W) {
+  if (const int r = wave; r < nr) {
     const double *row = sc + r * NP;
     const int64_t grow = (int64_t)bh * nB + r0 + r;
     double pl[E];
@@ -473,7 +476,6 @@ __global__ void __launch_bounds__(64 * W) select_kernel(const double *__restrict
           const double m_off = bs.m_hi;
           bisect_steps<1>(k1, p1, c_off, m_off, tauZ, 1, bs);
           kstar = bisect_result<1>(k1, c_off, bs, k);
-          __builtin_amdgcn_wave_barrier();  // the next row's compaction writes the same area
         }
       }
       cut = row[sel_index(kstar)];
@@ -546,7 +548,6 @@ static hipError_t launch_select_dr(const double *qbar, const double *kbar, int B
                                    hipStream_t s) {
   const int G = (nB + R - 1) / R * BH;
   dim3 grid((G + 7) / 8 * 8);
-  // the logits, then the pooled rows or phase 2's candidate buffers
   const int need = (nB + 63) / 64;  // positions per lane
   // the logits (rows padded to 64 E), then the pooled rows or phase 2's
   // candidate buffers
