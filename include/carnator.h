@@ -219,7 +219,10 @@ int carnator_compact_block_mask(const uint8_t *mask, const carnator_shape *shape
  * the softmax over all N keys, sigma = scale or 1/sqrt(head_dim) when
  * scale <= 0; n_i the valid queries of block i; each row sums to 1.  A dense
  * bf16 matrix-core pass (fp32 accumulation, exponentials and sums per key
- * block), the blocks' and the queries' sums in fp64.
+ * block), the blocks' and the queries' sums in fp64.  Queries whose scores
+ * climb about 100 (sigma q . k log2 e) above those of the first 32 keys, or
+ * inputs that are not finite, make the 256 or 512 queries around them take
+ * about 2.7 times the time.
  *
  * carnator_block_mass_exact:
  *   q_hist, k_hist  bf16 views [B, H, N, d]
@@ -449,7 +452,10 @@ int carnator_block_sparse_attn_rows(const carnator_view *q, const carnator_view 
  *   lse_a = log sum_{t in A(a)} exp(sigma * q_a . k_t),
  * sigma = scale, or 1/sqrt(head_dim) when scale <= 0.  A row with no kept
  * block gives o = 0 and lse = -inf.  bf16 matrix cores for Q.K^T and P.V,
- * fp32 accumulation and softmax; O is rounded to bf16.
+ * fp32 accumulation and softmax; O is rounded to bf16.  A query block with a
+ * query whose scores climb about 100 (sigma q . k log2 e) above those of its
+ * first listed keys, or with inputs that are not finite, takes about twice the
+ * time.
  *
  *   q, k, v        bf16 views [B, H, N, d]
  *   out            bf16 [B, H, N, d] at element strides out_stride_{b,h,n}

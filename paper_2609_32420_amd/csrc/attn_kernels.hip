@@ -107,7 +107,9 @@ struct Cfg {
   // under (48 heads x 17,776 tokens 2438 -> 2360 us, 6 x 4000 41.1 -> 37.0).
   // At d = 128 its 74 KB of LDS leave two workgroups per CU instead of three,
   // which costs more wherever there are more than two to run (24 x 8000
-  // tokens 565 -> 595 us, 12 x 4000 116 -> 142; 2 x 6 x 1988 42.7 -> 38.5).
+  // tokens 565 -> 595 us, 12 x 4000 116 -> 142).  The line is drawn by head
+  // size alone: a smaller grid would gain by the larger stage there too (2 x 6
+  // x 1988 42.7 -> 38.5 us), but not without a second kernel for it.
   static constexpr int KT = BS == 128 || D == 64 ? 64 : 32;
   static constexpr int SPB = BS / KT;             // stages per key block
   static constexpr int MT = KT / 32;              // 32-key MFMA tiles per stage
@@ -160,9 +162,12 @@ struct Cfg {
 // 17,776 tokens, d = 64, with the LSE 2027 -> 1851 us; lists at d = 128: 12
 // heads x 32,760 tokens 1673 -> 1618 us, 24 heads x 119,056 tokens 23.8 ->
 // 22.6 ms.
-// At d = 64 the kernel is held to 168 registers, so three workgroups share a
-// CU (their LDS, 3 x 40 KB, fits): with half the MFMAs per score of d = 128
-// it is bound by its vector work, which a third wave per SIMD overlaps better.
+// At d = 64 with 128-token blocks the kernel is held to 168 registers, so
+// three workgroups share a CU (their LDS, 3 x 40 KB, fits): with half the MFMAs
+// per score of d = 128 it is bound by its vector work, which a third wave per
+// SIMD overlaps better.  With 64-token blocks a workgroup is two waves and
+// three of them fill the CU's LDS (41 KB each), so up to 256 registers are free
+// (175 to 190 used).
 template <int D, int BS, bool WITH_LSE>
 __global__ void __launch_bounds__(2 * BS, D == 64 && BS == 128 ? 3 : 2)
 bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, int64_t osh,

@@ -339,11 +339,13 @@ __global__ void __launch_bounds__(256) mass_reduce_kernel(const float *__restric
 
 }  // namespace
 
-// The workspace holds 8 bytes per (query, key block) and 4 per query of a
-// head, for as many heads as fit kMassScratchCap (at least one), so it stays
-// bounded whatever the number of heads.  The pass writes 4-byte records: a
-// chunk takes about twice as many heads (34 MB each at 32K tokens, 443 MB at
-// 119K).
+// The entry point asks for 8 bytes per (query, key block) and 4 per query of a
+// head, for as many heads as fit kMassScratchCap (at least one), so the
+// workspace stays bounded whatever the number of heads.  The pass writes 4-byte
+// records (34 MB a head at 32K tokens, 443 MB at 119K), so a chunk takes about
+// twice as many heads, and where one chunk holds them all half of the workspace
+// is not touched: the size asked for stays what callers that keep a workspace
+// have always allocated.
 constexpr size_t kMassScratchCap = (size_t)4 << 30;
 
 size_t mass_scratch_bytes(int BH, int N, int nB) {
