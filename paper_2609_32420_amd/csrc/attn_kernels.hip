@@ -100,17 +100,28 @@ __device__ inline int swz_v(int r) {
 // limited to this by the entry points).
 constexpr int kMaxListBlocks = 2048;
 
-template <int D, int BS>
+// Keys per stage (KT): 64 with 128-token blocks, 32 with 64-token blocks at
+// d = 128 (there the larger tiles cost a third of the workgroups per CU: 24 x
+// 8000 tokens 565 -> 595 us, 12 x 4000 116 -> 142; a grid of at most two
+// workgroups per CU would gain, 2 x 6 x 1988 42.7 -> 38.5, but not without a
+// kernel of its own), and either with 64-token blocks at d = 64.  There 32 keys
+// are 8 MFMAs a wave, too few to load the next tiles under, but 64 leave three
+// workgroups per CU instead of six.  64 are taken where all workgroups run at
+// once all the same (R <= 3 x 256), and in ten rounds of long rows and more;
+// otherwise six smaller workgroups leave less of the chip idle in the last
+// round and hide more of the start of a short row.  64 against 32 keys, lists
+// of random pairs (r) or a band (b):
+//   12 heads x 4000 tokens (R = 756): r 20 % 24.1 against 27.4 us, all 67 / 74
+//   16 x 4000 (R = 1008): r 20 % 29.7 / 31.2, b 30 % 49.9 / 37.7, all 112 / 85
+//   48 x 4000 (R = 3024): r 5 % 35.1 / 33.7, r 20 % 86.9 / 81.1, all 266 / 256
+//   24 x 16,000 (R = 6000): r 5 % 169 / 168, r 20 % 589 / 575, b 30 % 749 / 809
+//   64 x 8000 (R = 8000): r 5 % 127 / 130, r 20 % 434 / 438, b 30 % 555 / 564
+//   32 x 16,000 (R = 8000): r 5 % 227 / 233, r 20 % 815 / 824, b 30 % 989 / 1088
+//   160 x 4000 (R = 10,080): r 5 % 111 / 107, r 20 % 297 / 303, b 30 % 397 / 396
+inline bool whole_block_stages(unsigned R, int nB) { return R <= 768 || (R >= 7680 && nB >= 120); }
+
+template <int D, int BS, int KT>
 struct Cfg {
-  // Keys per stage: half a key block, but a whole one at d = 64 with 64-token
-  // blocks: 32 keys there are 8 MFMAs a wave, too few to load the next tiles
-  // under (48 heads x 17,776 tokens 2438 -> 2360 us, 6 x 4000 41.1 -> 37.0).
-  // At d = 128 its 74 KB of LDS leave two workgroups per CU instead of three,
-  // which costs more wherever there are more than two to run (24 x 8000
-  // tokens 565 -> 595 us, 12 x 4000 116 -> 142).  The line is drawn by head
-  // size alone: a smaller grid would gain by the larger stage there too (2 x 6
-  // x 1988 42.7 -> 38.5 us), but not without a second kernel for it.
-  static constexpr int KT = BS == 128 || D == 64 ? 64 : 32;
   static constexpr int SPB = BS / KT;             // stages per key block
   static constexpr int MT = KT / 32;              // 32-key MFMA tiles per stage
   static constexpr int WAVES = BS / 32;
@@ -165,17 +176,17 @@ struct Cfg {
 // At d = 64 with 128-token blocks the kernel is held to 168 registers, so
 // three workgroups share a CU (their LDS, 3 x 40 KB, fits): with half the MFMAs
 // per score of d = 128 it is bound by its vector work, which a third wave per
-// SIMD overlaps better.  With 64-token blocks a workgroup is two waves and
-// three of them fill the CU's LDS (41 KB each), so up to 256 registers are free
-// (175 to 190 used).
-template <int D, int BS, bool WITH_LSE>
+// SIMD overlaps better.  With 64-token blocks a workgroup is two waves, and LDS
+// holds three of them (six with 32-key stages at d = 64), so registers (118 to
+// 190) do not limit them.
+template <int D, int BS, bool WITH_LSE, int KT>
 __global__ void __launch_bounds__(2 * BS, D == 64 && BS == 128 ? 3 : 2)
 bsattn_kernel(View q, View k, View v, uint16_t *__restrict__ out, int64_t osb, int64_t osh,
               int64_t osn, int H, int N, int nB, const int32_t *__restrict__ row_ptr,
               const int32_t *__restrict__ col_idx, const int32_t *__restrict__ order,
               const int32_t *__restrict__ n_rows, float c2, float *__restrict__ lse) {
-  using C = Cfg<D, BS>;
-  constexpr int KT = C::KT, MT = C::MT;
+  using C = Cfg<D, BS, KT>;
+  constexpr int MT = C::MT;
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
   // a row subset: only order[0 .. *n_rows) (the whole workgroup, before any
   // barrier)
@@ -683,24 +694,25 @@ hipError_t launch_bsattn(View q, View k, View v, uint16_t *out, int64_t osb, int
   const unsigned R = (unsigned)B * H * nB;
   const float c2 = scale * 1.4426950408889634f;
   hipError_t e = hipSuccess;
-#define CARNATOR_BSATTN_L(DD, BB, LL)                                                             \
+#define CARNATOR_BSATTN_L(DD, BB, LL, KK)                                                         \
   do {                                                                                            \
-    using C = Cfg<DD, BB>;                                                                        \
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&bsattn_kernel<DD, BB, LL>),           \
+    using C = Cfg<DD, BB, KK>;                                                                    \
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&bsattn_kernel<DD, BB, LL, KK>),       \
                             hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);                  \
     if (e != hipSuccess) return e;                                                                \
-    hipLaunchKernelGGL((bsattn_kernel<DD, BB, LL>), dim3(R), dim3(C::NT), C::LDS, s, q, k, v,     \
+    hipLaunchKernelGGL((bsattn_kernel<DD, BB, LL, KK>), dim3(R), dim3(C::NT), C::LDS, s, q, k, v, \
                        out, osb, osh, osn, H, N, nB, row_ptr, col_idx, order, n_rows, c2, lse);   \
   } while (0)
-#define CARNATOR_BSATTN(DD, BB)                  \
-  do {                                           \
-    if (lse) CARNATOR_BSATTN_L(DD, BB, true);    \
-    else CARNATOR_BSATTN_L(DD, BB, false);       \
+#define CARNATOR_BSATTN(DD, BB, KK)                  \
+  do {                                               \
+    if (lse) CARNATOR_BSATTN_L(DD, BB, true, KK);    \
+    else CARNATOR_BSATTN_L(DD, BB, false, KK);       \
   } while (0)
-  if (d == 128 && bs == 128) CARNATOR_BSATTN(128, 128);
-  else if (d == 128 && bs == 64) CARNATOR_BSATTN(128, 64);
-  else if (d == 64 && bs == 128) CARNATOR_BSATTN(64, 128);
-  else CARNATOR_BSATTN(64, 64);
+  if (d == 128 && bs == 128) CARNATOR_BSATTN(128, 128, 64);
+  else if (d == 128 && bs == 64) CARNATOR_BSATTN(128, 64, 32);
+  else if (d == 64 && bs == 128) CARNATOR_BSATTN(64, 128, 64);
+  else if (whole_block_stages(R, nB)) CARNATOR_BSATTN(64, 64, 64);
+  else CARNATOR_BSATTN(64, 64, 32);
 #undef CARNATOR_BSATTN
 #undef CARNATOR_BSATTN_L
   return hipGetLastError();

@@ -398,3 +398,55 @@ def test_attention_lse_beside_a_large_reference(d, bs):
     err = float((lse.double() - np.log(4.0)).abs().max())
     print("lse error", d, bs, err)
     assert err <= 5e-7
+
+
+# d = 64 with 64-token blocks takes stages of a whole block or of half of one
+# by the number of rows (768, 7680) and of key blocks (120): each side of each
+# line, with a ragged last block and an infinite value in the block before it
+# that half of the lists leave out.  P and O are rounded to bf16 (2^-9 each of
+# values up to 4), the LSE carries fp32 roundings only.
+@pytest.mark.parametrize("heads,n", [(768, 40), (769, 40), (256, 190), (257, 190), (64, 120 * 64 - 9),
+                                     (63, 120 * 64 - 9), (65, 119 * 64 - 9)])
+def test_attention_stage_rule(heads, n):
+    print("attention stages", heads, n, flush=True)
+    d = bs = 64
+    nb = -(-n // bs)
+    g = torch.Generator(device=DEV).manual_seed(n + heads)
+    q, k, v = (torch.randn(1, heads, n, d, generator=g, device=DEV).to(torch.bfloat16) for _ in range(3))
+    m = (torch.rand(1, heads, nb, nb, generator=g, device=DEV) < 0.1).to(torch.uint8)
+    m[..., -1] = 1
+    if nb > 1:
+        v[..., (nb - 1) * bs - 3, 7] = float("inf")
+        m[..., ::2, nb - 2] = 0
+        m[..., 1::2, nb - 2] = 1
+    o, lse = P.block_sparse_attn(q, k, v, m, bs, return_lse=True)
+    holds = (torch.arange(n, device=DEV) // bs % 2 == 1) & (nb > 1)
+    assert torch.equal(torch.isinf(o[..., 7]), holds.expand(1, heads, n))
+    o[..., 7] = v[..., 7] = 0
+    assert torch.isfinite(o).all()
+    v = v.double()
+    for h in (0, heads // 2, heads - 1):
+        for i in (0, nb // 2, nb - 1):
+            rows = slice(i * bs, min((i + 1) * bs, n))
+            keep = m[0, h, i].repeat_interleave(bs)[:n].bool().cpu()
+            x = (q[0, h, rows].double().cpu() @ k[0, h].double().cpu().T.contiguous()) / d ** 0.5
+            x = x.masked_fill(~keep, float("-inf"))
+            want = torch.softmax(x, -1) @ v[0, h].cpu()
+            assert (o[0, h, rows].double().cpu() - want).abs().max() <= 2e-2
+            assert (lse[0, h, rows].double().cpu() - torch.logsumexp(x, -1)).abs().max() <= 1e-5
+
+
+# One third more rows than three workgroups per CU take a third more time, not
+# a second round: 12 and 16 heads of 63 rows, a band of 30 % of the pairs.
+def test_attention_time_past_three_workgroups_per_cu():
+    n, d, bs, nb = 4000, 64, 64, 63
+    i = torch.arange(nb, device=DEV)
+    band = ((i[:, None] - i[None]).abs() <= 0.15 * nb).to(torch.uint8)
+    calls = []
+    for heads in (12, 16):
+        q, k, v = _shifted(heads, n, d, 0.0, 0.0)
+        lists = P.compact_block_mask(band.expand(1, heads, nb, nb).contiguous())
+        calls.append(lambda q=q, k=k, v=v, lists=lists: [P.block_sparse_attn_lists(q, k, v, lists, bs) for _ in range(20)])
+    a, b = _times(calls)
+    print("attention 12 heads %.1f us, 16 heads %.1f us" % (a / 20, b / 20), flush=True)
+    assert b <= 1.5 * a
